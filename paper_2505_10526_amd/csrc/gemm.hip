@@ -316,12 +316,13 @@ void gemm_vocab_kernel(GemmDev g) {
     }
     // EPI_ARGMAX, EPI_LOGITS_STATS: largest summed output (and its lowest column) seen by this lane for row
     // 16 mt + lr; EPI_LOGITS_STATS: also the sum of exp((x - largest)/T) over what the lane has seen (rescaled
-    // whenever the largest moves)
+    // whenever the largest moves): four terms at a time in fp32, the rest in double, over all of the workgroup's shares.
     constexpr bool STATS = (EPI == EPI_LOGITS_STATS);
-    float best_v[MT], sum_e[MT];
+    float best_v[MT];
+    double sum_e[MT];
     int best_i[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) { best_v[mt] = -INFINITY; best_i[mt] = INT_MAX; sum_e[mt] = 0.f; }
+    for (int mt = 0; mt < MT; ++mt) { best_v[mt] = -INFINITY; best_i[mt] = INT_MAX; sum_e[mt] = 0.0; }
 
     // Barrier for what travels through LDS; loads on their way into registers stay on their way.
     auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
@@ -376,13 +377,16 @@ void gemm_vocab_kernel(GemmDev g) {
                     const int m = mt * 16 + lr;
                     const int col = (first + nt) * 16 + lc * 4;      // 4 consecutive output features
                     if (EPI == EPI_ARGMAX || STATS) {
+const float before = best_v[mt];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {                 // ascending columns: a tie keeps the lower one
-                            if constexpr (STATS) {
-                                if (s[i] > best_v[mt]) sum_e[mt] = sum_e[mt] * exp2_scaled(best_v[mt] - s[i], g.ts_hi, g.ts_lo) + 1.f;
-                                else sum_e[mt] += exp2_scaled(s[i] - best_v[mt], g.ts_hi, g.ts_lo);
-                            }
+                        for (int i = 0; i < 4; ++i)                   // ascending columns: a tie keeps the lower one
                             if (s[i] > best_v[mt] || (s[i] == best_v[mt] && col + i < best_i[mt])) { best_v[mt] = s[i]; best_i[mt] = col + i; }
+                        if constexpr (STATS) {
+                            float four = 0.f;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) four += exp2_scaled(s[i] - best_v[mt], g.ts_hi, g.ts_lo);
+                            if (best_v[mt] > before) sum_e[mt] *= (double)exp2_scaled(before - best_v[mt], g.ts_hi, g.ts_lo);
+                            sum_e[mt] += (double)four;
                         }
                         if (STATS && m < g.M) *reinterpret_cast<floatx4*>((float*)g.y + (size_t)m * g.ldy + col) = s;
                     } else if (m < g.M) {
@@ -397,18 +401,18 @@ void gemm_vocab_kernel(GemmDev g) {
         lds_barrier();                                           // the reduction buffer is free
         float* bv = reinterpret_cast<float*>(red);               // [WK][MT*16]
         int* bi = reinterpret_cast<int*>(bv + WK * MT * 16);
-        float* bs = reinterpret_cast<float*>(bi + WK * MT * 16);
+        double* bs = reinterpret_cast<double*>(bi + WK * MT * 16);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            float v = best_v[mt], se = sum_e[mt]; int i = best_i[mt];
+            float v = best_v[mt]; double se = sum_e[mt]; int i = best_i[mt];
 #pragma unroll
             for (int o = 16; o <= 32; o <<= 1) {
                 const float ov = __shfl_xor(v, o, kWave);
                 const int oi = __shfl_xor(i, o, kWave);
                 if constexpr (STATS) {
-                    const float os = __shfl_xor(se, o, kWave);
+                    const double os = __shfl_xor(se, o, kWave);
                     const float mn = fmaxf(v, ov);
-                    se = (mn == -INFINITY) ? 0.f : se * exp2_scaled(v - mn, g.ts_hi, g.ts_lo) + os * exp2_scaled(ov - mn, g.ts_hi, g.ts_lo);
+                    se = (mn == -INFINITY) ? 0.0 : se * (double)exp2_scaled(v - mn, g.ts_hi, g.ts_lo) + os * (double)exp2_scaled(ov - mn, g.ts_hi, g.ts_lo);
                 }
                 if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
             }
@@ -425,7 +429,7 @@ void gemm_vocab_kernel(GemmDev g) {
             if constexpr (STATS) {                               // wave order, in double
                 for (int w = 0; w < WK; ++w)
                     if (bv[w * MT * 16 + tid] > -INFINITY)
-                        r.s += (double)bs[w * MT * 16 + tid] * (double)exp2_scaled(bv[w * MT * 16 + tid] - v, g.ts_hi, g.ts_lo);
+                        r.s += bs[w * MT * 16 + tid] * (double)exp2_scaled(bv[w * MT * 16 + tid] - v, g.ts_hi, g.ts_lo);
             }
             reinterpret_cast<RowPartial*>(STATS ? g.stats : g.y)[(size_t)tid * gridDim.x + blockIdx.x] = r;
         }

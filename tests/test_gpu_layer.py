@@ -475,3 +475,26 @@ def test_vocabulary_projection_in_shares(M, H, V):
         torch.cuda.synchronize()
         assert torch.equal(logits, got)
         assert (drawn == apart).float().mean() >= 0.9              # a draw within rounding of a boundary may differ
+
+
+def test_vocabulary_statistics_carried_across_shares_keep_small_terms():
+    """The records (maximum, its column, sum of exp(x - maximum)) that the sampled projection leaves at the head of its
+    workspace, behind the packed rows: one per workgroup, 256 where each works off several shares.  Four tokens in forty have
+    logit 0, the others -17.25, so that a sum kept in fp32 takes on 4.0 and loses every small term after it (2.9e-7 of the
+    total); the bound is the fp32 error of those terms, 2e-6 of that share."""
+    H, V, T = 32, 152064, 1.0
+    w = torch.zeros(V, H, device="cuda", dtype=torch.bfloat16)
+    w[:, 0] = -17.25
+    w[torch.arange(V, device="cuda") % 40 < 4, 0] = 0.0
+    x = torch.zeros(1, 1, H, device="cuda", dtype=torch.bfloat16)
+    x[..., 0] = 1.0
+    ws = torch.full((binding.load().massv_lm_head_accept_workspace(1, 0, H, V, binding.BF16),), 255, dtype=torch.uint8, device="cuda")
+    _, _, logits = binding.lm_head_accept(x, None, binding.weight_pack(w), None, None, torch.full((1, 1), 0.5, device="cuda"), T, ws=ws)
+    torch.cuda.synchronize()
+    head = 16 * H * 2
+    rec = ws[head:head + 256 * 16].cpu().numpy().view(np.dtype([("m", "<f4"), ("arg", "<i4"), ("s", "<f8")]))
+    assert np.all(rec["m"] == 0.0) and len(set(rec["arg"].tolist())) == 256
+    n0 = sum(n % 40 < 4 for n in range(V))
+    want = n0 + (V - n0) * np.exp(-17.25)
+    assert abs(rec["s"].sum() / want - 1) <= 2e-6 * 2.9e-7 + 1e-12
+    assert torch.equal(logits[0], w[:, 0].float())
