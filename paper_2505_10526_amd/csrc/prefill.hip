@@ -363,9 +363,10 @@ void prefill_attention_kernel(PrefillParams p) {
 // 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
 // ---------------------------------------------------------------------------
 constexpr int kPfRing = 4;
+typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));      // 16 bytes from any address
 constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 128 KB at d = 256
 
-template <int D>
+template <int D, bool DIRECT>
 __global__ __launch_bounds__(kPfThreads)
 void prefill_attention_lds_kernel(PrefillParams p) {
     constexpr int KS = D / 16, NT = D / 32, BP = D * 4;      // BP: 16-byte pieces of a block's keys (or values)
@@ -398,17 +399,22 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     const int blk_end = (pf_hi(L + pos_of(w0 + kPfWaves * 32 - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
 
     extern __shared__ bf16x8 pf_lds[];                                // [kPfRing][keys | values][BP]
-    const bf16x8* const kc = reinterpret_cast<const bf16x8*>(p.kc + bg * (size_t)p.l_max * D) + tid;
-    const bf16x8* const vc = reinterpret_cast<const bf16x8*>(p.vc + bg * (size_t)p.l_max * D) + (tid ^ ((tid / 16) % 4));
-    auto dma = [&](const bf16x8* src, bf16x8* dst) {
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    // DIRECT: caches that start at a multiple of 16 bytes.  Others travel through registers (a load to LDS takes 16 bytes
+    // from a multiple of 16 only; an ordinary load takes them from anywhere).
+    const bf16_t* const kc = p.kc + bg * (size_t)p.l_max * D + tid * 8;
+    const bf16_t* const vc = p.vc + bg * (size_t)p.l_max * D + (tid ^ ((tid / 16) % 4)) * 8;
+    auto bring = [&](const bf16_t* src, bf16x8* dst) {
+        if constexpr (DIRECT)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+        else
+            dst[lane] = *reinterpret_cast<const bf16x8_any*>(src);
     };
     auto request = [&](int blk) {
         bf16x8* dst = pf_lds + (size_t)(blk % kPfRing) * 2 * BP + wave * kWave;
 #pragma unroll
-        for (int u = 0; u < NL; ++u) dma(kc + (size_t)blk * BP + u * kPfThreads, dst + u * kPfThreads);
+        for (int u = 0; u < NL; ++u) bring(kc + ((size_t)blk * BP + u * kPfThreads) * 8, dst + u * kPfThreads);
 #pragma unroll
-        for (int u = 0; u < NL; ++u) dma(vc + (size_t)blk * BP + u * kPfThreads, dst + BP + u * kPfThreads);
+        for (int u = 0; u < NL; ++u) bring(vc + ((size_t)blk * BP + u * kPfThreads) * 8, dst + BP + u * kPfThreads);
     };
     auto barrier = [&]() {
         __builtin_amdgcn_sched_barrier(0);
@@ -418,7 +424,8 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     // Opens block blk: block blk + 1 has landed for every wave (a wave's requests complete in order; those of blk + 2 may
     // still be on their way), everybody is done with block blk - 1, and its place takes block blk + 3.
     auto open = [&](int blk) {
-        if (blk + 2 < blk_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
+        if (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else if (blk + 2 < blk_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         barrier();
         if (blk + 3 < blk_end) request(blk + 3);
@@ -517,7 +524,7 @@ void prefill_attention_lds_kernel(PrefillParams p) {
             for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0[nt][t], pv[t], acc[nt], 0, 0, 0);
     };
 
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     barrier();
     int blk = blk_begin;
     for (; blk < blk_first; ++blk) open(blk);      // blocks that only the rows of other waves see
@@ -652,14 +659,14 @@ static int launch_prefill(const massv_attn_desc& a, PrefillParams p, hipStream_t
     return launch_status();
 }
 
-template <int D>
+template <int D, bool DIRECT>
 static int launch_prefill_lds(const massv_attn_desc& a, PrefillParams p, hipStream_t st) {
     // more LDS than a kernel gets by default: the limit is raised once per device
     static std::atomic<bool> ready[64];           // zero-initialised; calls may come from several threads
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MASSV_ELAUNCH;
     if (!ready[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void*)prefill_attention_lds_kernel<D>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void*)prefill_attention_lds_kernel<D, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)pf_lds_bytes(D)) != hipSuccess) return MASSV_ELAUNCH;
         ready[dev].store(true, std::memory_order_release);
     }
@@ -667,9 +674,14 @@ static int launch_prefill_lds(const massv_attn_desc& a, PrefillParams p, hipStre
     const int per_wg = kPfWaves * 32;
     p.n_tiles = (rows_max + per_wg - 1) / per_wg;
     if (p.n_tiles > 65535) return MASSV_EUNSUPPORTED;
-    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_lds_kernel<D>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
+    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_lds_kernel<D, DIRECT>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
                   dim3(kPfThreads), pf_lds_bytes(D), st, p);
     return launch_status();
+}
+template <int D>
+static int launch_prefill_lds(const massv_attn_desc& a, const PrefillParams& p, hipStream_t st) {
+    const bool direct = ((uintptr_t)p.kc | (uintptr_t)p.vc) % 16 == 0;
+    return direct ? launch_prefill_lds<D, true>(a, p, st) : launch_prefill_lds<D, false>(a, p, st);
 }
 
 }  // namespace massv

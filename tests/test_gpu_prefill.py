@@ -140,3 +140,25 @@ def test_both_sides_of_the_launch_size_rule(heads, n_new):
     """258, 256 and 264 workgroups of 256 stacked rows: the kernel with 64 rows per wave above 256, the other up to it."""
     s = synth.LayerShape(256, heads[0], heads[1], 64, 704, 4096, dtype="bf16")
     run_case(s, [0] * len(n_new), n_new, [9] * len(n_new), seed=len(n_new), check=[0, len(n_new) - 1])
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("heads,n_new", [((6, 2), [43, 86, 1]), ((8, 1), [33, 16])])
+def test_caches_that_start_anywhere(heads, n_new, d):
+    """Caches, queries and output as slices of larger buffers, one and four elements off a multiple of 16 bytes: blocks
+    then go to LDS through registers instead of by direct loads, with the same bits."""
+    B, kv_len = len(n_new), [40, 7, 100][:len(n_new)]
+    l_max = round_up(max(a + b for a, b in zip(kv_len, n_new)), 32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    rn = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = rn(B, max(n_new), heads[0], d), rn(B, heads[1], l_max, d), rn(B, heads[1], l_max // 32, d, 32)
+    out = []
+    for off in (0, 1, 4):
+        def put(t):
+            view = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)[off:off + t.numel()].view(t.shape)
+            view.copy_(t)
+            return view
+        out.append(binding.prefill_attention(put(q), put(k), put(v), i32(kv_len), i32(n_new), out=put(torch.zeros_like(q))))
+    torch.cuda.synchronize()
+    assert out[0].abs().sum() > 0 and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
