@@ -7,8 +7,10 @@ library is missing, `load()` raises.
 """
 from __future__ import annotations
 
+import collections
 import ctypes as C
 import os
+import threading
 from dataclasses import dataclass
 
 import torch
@@ -169,16 +171,47 @@ def dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-_workspaces: dict = {}
+class _Scratch(threading.local):
+    """One thread's scratch buffers, by (device, stream), the least recently used first."""
+    LIMIT = 8                       # streams; a call on a ninth gives back the buffer of the one used longest ago
+
+    def __init__(self):
+        self.buffers = collections.OrderedDict()
+
+
+_scratch = _Scratch()
+_recorded: list = []                # buffers that a recorded graph may use: kept for good
+
+
+def _stream_handle():
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _capturing():
+    return torch.cuda.is_current_stream_capturing()
 
 
 def workspace(nbytes: int, device) -> torch.Tensor:
-    """A reusable scratch buffer of at least nbytes on `device`."""
-    key = (torch.device(device).index or 0)
-    ws = _workspaces.get(key)
-    if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(max(int(nbytes), 1 << 20), dtype=torch.uint8, device=device)
-        _workspaces[key] = ws
+    """A scratch buffer of at least nbytes on `device` for a call on the current stream.  Calls of one thread on one stream
+    follow each other, so they share a buffer; another stream or thread has its own.  A buffer that is outgrown or
+    dropped was allocated on the stream that used it, and so is reused only behind that stream's work.  While the stream is
+    captured, a new buffer belongs to the graph's memory and is not kept here."""
+    device = torch.device(device)
+    if device.type == "cuda" and device.index is None:
+        device = torch.device("cuda", torch.cuda.current_device())
+    key = (device, _stream_handle())
+    ws = _scratch.buffers.get(key)
+    if ws is not None and ws.numel() >= nbytes:
+        _scratch.buffers.move_to_end(key)
+        if _capturing() and not any(ws is r for r in _recorded):
+            _recorded.append(ws)
+        return ws
+    ws = torch.empty(max(int(nbytes), 1 << 20), dtype=torch.uint8, device=device)
+    if not _capturing():
+        _scratch.buffers[key] = ws
+        _scratch.buffers.move_to_end(key)
+        if len(_scratch.buffers) > _scratch.LIMIT:
+            _scratch.buffers.popitem(last=False)
     return ws
 
 
