@@ -442,9 +442,11 @@ size_t massv_linear_workspace(int32_t M, int32_t N, int32_t K, int32_t dtype);
 /* x [M][K] row-major (dtype) in; w [N][K] (dtype) in the streaming layout of massv_weight_pack;
  * bias [N] (dtype) or NULL; y [M][N] row-major (dtype) out; all device pointers.  fp32 accumulation, one
  * rounding to dtype after the activation.  bf16 only; K % 64 == 0 and N % 16 == 0, any M >= 1, else
- * MASSV_EUNSUPPORTED.  The workspace holds fp32 partial sums where K is split over workgroups (few rows); any size
+ * MASSV_EUNSUPPORTED.  The workspace has room for X once (for a copy, if x does not start at a multiple of 16 bytes or
+ * y overlaps it) and, behind that, for the fp32 partial sums of a K that is split over workgroups (few rows).  Any size
  * from ceil(M / 16) * 16 * K elements of dtype (rounded up to 256 bytes) is taken, massv_linear_workspace() is the size
- * with which K can be split as far as pays.  The order of the sums, and so the last bit, depends on it. */
+ * with which K can be split as far as pays; more than that changes nothing.  With less, the order of the sums, and so the
+ * last bit, depends on the size. */
 int massv_linear(const void* x, const void* w, const void* bias, void* y, int32_t M, int32_t N, int32_t K,
                  int32_t act, int32_t dtype, void* workspace, size_t workspace_bytes, void* stream);
 
