@@ -14,6 +14,7 @@ constexpr int kWave = 64;          // CDNA wavefront width
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));      // 16 bytes in one access, from any address
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 

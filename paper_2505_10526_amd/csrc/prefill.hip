@@ -363,7 +363,6 @@ void prefill_attention_kernel(PrefillParams p) {
 // 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
 // ---------------------------------------------------------------------------
 constexpr int kPfRing = 4;
-typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));      // 16 bytes from any address
 constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 128 KB at d = 256
 
 template <int D, bool DIRECT>

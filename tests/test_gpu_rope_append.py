@@ -179,7 +179,7 @@ def test_blocks_of_rows_equal_the_general_path(d, n_q, n_kv, sections, norm):
         assert norm or name == "v" and np.array_equal(a, b) or np.mean(a != b) <= 2.0 ** -13, (name, np.mean(a != b))
 
 
-@pytest.mark.parametrize("M,H", [(1, 8), (3, 504), (5, 512), (4, 520), (33, 2048), (7, 2056), (9, 4096), (2, 4104), (6, 8192), (3, 8200), (5, 77)])
+@pytest.mark.parametrize("M,H", [(1, 8), (6, 248), (6, 256), (3, 504), (5, 512), (4, 520), (33, 2048), (7, 2056), (9, 4096), (2, 4104), (6, 8192), (3, 8200), (5, 77)])
 def test_rmsnorm_row_widths(M, H):
     """Rows that a wave holds in 4, 8 or 16 pieces a lane, wider ones and ones no 16-byte piece divides, and operands off
     their alignment, against float64; the bound is one bf16 rounding (2^-9) and fp32 sums of H squares."""
@@ -189,6 +189,23 @@ def test_rmsnorm_row_widths(M, H):
     xd, gd = to_dev(x, "bf16"), to_dev(g, "bf16")
     off = torch.empty(M * H + 8, dtype=torch.bfloat16, device="cuda")[3:3 + M * H].view(M, H)
     off.copy_(xd)
-    for t in (xd, off):
-        y = binding.rmsnorm(t, gd).float().cpu().numpy()
+    got = [binding.rmsnorm(t, gd).float().cpu().numpy() for t in (xd, off)]
+    for y in got:
         assert np.all(np.abs(y - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-6)
+    assert np.array_equal(*got)
+
+
+@pytest.mark.parametrize("H", [512, 3584, 8192])
+def test_rmsnorm_bits_do_not_depend_on_the_address(H):
+    """2000 rows, operands up to seven elements off a multiple of 16 bytes: the order of a row's sum is the same."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H)
+    x, gain = torch.randn(2000, H, generator=g, device="cuda").to(torch.bfloat16), torch.randn(H, generator=g, device="cuda").to(torch.bfloat16)
+
+    def put(t, off):
+        view = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)[off:off + t.numel()].view(t.shape)
+        view.copy_(t)
+        return view
+    want = binding.rmsnorm(x, gain)
+    for a, b, c in ((1, 0, 0), (0, 4, 0), (0, 0, 7), (3, 5, 2)):
+        assert torch.equal(binding.rmsnorm(put(x, a), put(gain, b), out=put(x, c)), want), (a, b, c)
