@@ -251,7 +251,7 @@ __global__ void rope_rows_kernel(const T* __restrict__ qkv, const int32_t* __res
 //   * a key's 8 features are the 16 bytes that the blocked key cache keeps together;
 //   * values are turned around in LDS so that a thread stores 8 rows of one feature, 16 bytes of the blocked value cache
 //     (single elements where fewer than 8 of them are new rows).
-// Bound by HBM for a batch of prompts: 16384 rows x 36 heads of 128 (300 MB) 252 -> 67 us.
+// Operands may start at any address.  Bound by HBM for a batch of prompts: 16384 rows x 36 heads of 128 (300 MB) 252 -> 67 us.
 template <int D>
 __global__ __launch_bounds__(2 * D)
 void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restrict__ pos, int n_pos, size_t pos_stride,
@@ -277,8 +277,8 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
         const int g = blockIdx.y - rotary_groups;
         if (live) {
             const bf16_t* vs = src + (size_t)(rotary + g) * D;
-            *reinterpret_cast<bf16x8*>(&vt[r][j]) = *reinterpret_cast<const bf16x8*>(vs);
-            *reinterpret_cast<bf16x8*>(&vt[r][j + HALF]) = *reinterpret_cast<const bf16x8*>(vs + HALF);
+            *reinterpret_cast<bf16x8*>(&vt[r][j]) = *reinterpret_cast<const bf16x8_any*>(vs);
+            *reinterpret_cast<bf16x8*>(&vt[r][j + HALF]) = *reinterpret_cast<const bf16x8_any*>(vs + HALF);
         }
         __syncthreads();
         bf16_t* dst = v_cache + v_cache_index((size_t)b * n_kv + g, l_max, D, row0, 0);
@@ -290,7 +290,7 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
                 bf16x8 o;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = vt[r0 + e][c];
-                *reinterpret_cast<bf16x8*>(dst + (size_t)c * MASSV_V_BLOCK + r0) = o;
+                *reinterpret_cast<bf16x8_any*>(dst + (size_t)c * MASSV_V_BLOCK + r0) = o;
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -310,12 +310,12 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
         sincos((double)pos[(size_t)comp * pos_stride + m] * freq[j + e], &sn[e], &cs[e]);
     }
     const int h0 = blockIdx.y * heads_per, h1 = h0 + heads_per < rotary ? h0 + heads_per : rotary;
-    bf16x8 a = *reinterpret_cast<const bf16x8*>(src + (size_t)h0 * D), c = *reinterpret_cast<const bf16x8*>(src + (size_t)h0 * D + HALF);
+    bf16x8 a = *reinterpret_cast<const bf16x8_any*>(src + (size_t)h0 * D), c = *reinterpret_cast<const bf16x8_any*>(src + (size_t)h0 * D + HALF);
     for (int head = h0; head < h1; ++head) {
         const bf16x8 a0 = a, c0 = c;
         if (head + 1 < h1) {                             // the next head's piece is on its way while this one is turned
-            a = *reinterpret_cast<const bf16x8*>(src + (size_t)(head + 1) * D);
-            c = *reinterpret_cast<const bf16x8*>(src + (size_t)(head + 1) * D + HALF);
+            a = *reinterpret_cast<const bf16x8_any*>(src + (size_t)(head + 1) * D);
+            c = *reinterpret_cast<const bf16x8_any*>(src + (size_t)(head + 1) * D + HALF);
         }
         float x1[8], x2[8];
 #pragma unroll
@@ -339,12 +339,12 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
         }
         if (head < n_q) {
             bf16_t* dst = q_out + (m * n_q + head) * D + j;
-            *reinterpret_cast<bf16x8*>(dst) = y1;
-            *reinterpret_cast<bf16x8*>(dst + HALF) = y2;
+            *reinterpret_cast<bf16x8_any*>(dst) = y1;
+            *reinterpret_cast<bf16x8_any*>(dst + HALF) = y2;
         } else {
             const size_t bg = (size_t)b * n_kv + (head - n_q);
-            *reinterpret_cast<bf16x8*>(k_cache + k_cache_index(bg, l_max, D, row, j)) = y1;
-            *reinterpret_cast<bf16x8*>(k_cache + k_cache_index(bg, l_max, D, row, j + HALF)) = y2;
+            *reinterpret_cast<bf16x8_any*>(k_cache + k_cache_index(bg, l_max, D, row, j)) = y1;
+            *reinterpret_cast<bf16x8_any*>(k_cache + k_cache_index(bg, l_max, D, row, j + HALF)) = y2;
         }
     }
 }
@@ -624,10 +624,9 @@ extern "C" int massv_rope_append(const massv_attn_desc* desc, const void* qkv, c
     const int64_t M = (int64_t)a.batch * a.n_query;
     if (M > 0x7fffffff || a.n_q_heads + 2 * a.n_kv_heads > 65535) return MASSV_EUNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
-    // bf16 rows in 16-byte pieces: everything that is read or written that way has to start at a multiple of 16 bytes
     const int n_blk = (a.n_query + MASSV_V_BLOCK - 1) / MASSV_V_BLOCK + 1;      // cache blocks that L_q rows can touch
-    if (a.dtype == MASSV_BF16 && ((uintptr_t)qkv | (uintptr_t)q_out | (uintptr_t)k_cache | (uintptr_t)v_cache) % 16 == 0 &&
-        (int64_t)a.batch * n_blk <= 0x7fffffff) {
+    // (a launch has fewer than 2^32 threads, and a grid fewer than 2^31 workgroups in x)
+    if (a.dtype == MASSV_BF16 && (int64_t)a.batch * n_blk * ((a.n_q_heads + a.n_kv_heads + 1) / 2 + a.n_kv_heads) * 2 * a.head_dim <= 0xffffffffll) {
         // rotary heads per workgroup: the more, the fewer times an angle is worked out; at least two workgroups per
         // compute unit before that counts
         int heads_per = 8;

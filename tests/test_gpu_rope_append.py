@@ -146,15 +146,17 @@ def test_rows_that_would_pass_the_end_of_the_cache_are_dropped():
     assert q[0, :24].abs().sum() > 0 and not q[0, 24:].any() and not q[1].any()
 
 
-@pytest.mark.parametrize("d,n_q,n_kv,sections,norm", [(64, 3, 1, None, False), (128, 28, 4, (16, 24, 24), False),
-                                                      (256, 16, 8, None, True), (128, 1, 1, None, True), (64, 40, 8, (8, 12, 12), False)])
-def test_blocks_of_rows_equal_the_general_path(d, n_q, n_kv, sections, norm):
-    """bf16 operands that start at a multiple of 16 bytes go by cache blocks, others element by element: the same queries
-    and the same whole caches from both.  Lengths that start and end anywhere in a block of 32, no row, one row, a full
-    cache, a cache that the rows would pass.  Both rotate in double; a result may differ by one bf16 step (2^-8 relative),
-    seldom without head norms, whose sums of squares are taken in another order."""
-    B, L, l_max = 7, 77, 160
-    kv_len, n_new = i32([0, 5, 31, 32, 83, 130, 60]), i32([77, 1, 33, 0, 77, 77, 76])
+@pytest.mark.parametrize("d,n_q,n_kv,sections,norm,copies", [(64, 3, 1, None, False, 9), (128, 28, 4, (16, 24, 24), False, 1),
+                                                             (256, 16, 8, None, True, 1), (128, 1, 1, None, True, 9), (64, 40, 8, (8, 12, 12), False, 1)])
+def test_blocks_of_rows_equal_the_general_path(d, n_q, n_kv, sections, norm, copies):
+    """Many bf16 rows go by cache blocks, few of them element by element: the same queries and the same whole caches from
+    one call for all sequences as from a call for each.  Lengths that start and end anywhere in a block of 32, no row, one
+    row, a full cache, a cache that the rows would pass.  Both rotate in double and copy the values; a rotated result may
+    differ by one bf16 step (2^-8 relative), seldom without head norms, whose sums of squares are taken in another order.
+    The same bits from operands one and four elements off a multiple of 16 bytes."""
+    L, l_max = 77, 160
+    kv_len, n_new = i32([0, 5, 31, 32, 83, 130, 60] * copies), i32([77, 1, 33, 0, 77, 77, 76] * copies)
+    B = len(kv_len)
     g = torch.Generator(device="cuda")
     g.manual_seed(d + n_q)
     rn = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
@@ -162,7 +164,7 @@ def test_blocks_of_rows_equal_the_general_path(d, n_q, n_kv, sections, norm):
     k0, v0 = rn(B, n_kv, l_max, d), rn(B, n_kv, l_max // 32, d, 32)
     pos = torch.randint(0, 4000, (B, L) if sections is None else (3, B, L), generator=g, device="cuda", dtype=torch.int32)
     out = []
-    for off in (0, 4):
+    for off in (0, 1, 4):
         def put(t):
             buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
             v = buf[off:off + t.numel()].view(t.shape)
@@ -170,13 +172,21 @@ def test_blocks_of_rows_equal_the_general_path(d, n_q, n_kv, sections, norm):
             return v
         k, v, q = put(k0), put(v0), put(torch.zeros(B, L, n_q, d, dtype=torch.bfloat16, device="cuda"))
         binding.rope_append(put(qkv), pos, kv_len, n_new, k, v, n_q, 1e6, sections, *norms, q_out=q)
-        torch.cuda.synchronize()
-        out.append([t.float().cpu().numpy() for t in (q, k, v)])
-    assert not np.array_equal(out[0][1], k0.float().cpu().numpy())
-    for a, b, name in zip(*out, "qkv"):
-        assert np.all(np.abs(a - b) <= 2.0 ** -7 * np.abs(b) + 1e-6), name
+        out.append((q, k, v))
+    k, v, q = k0.clone(), v0.clone(), torch.zeros(B, L, n_q, d, dtype=torch.bfloat16, device="cuda")
+    for b in range(B):
+        s = slice(b, b + 1)
+        binding.rope_append(qkv[s], pos[..., s, :].contiguous(), kv_len[s], n_new[s], k[s], v[s], n_q, 1e6, sections, *norms, q_out=q[s])
+    torch.cuda.synchronize()
+    for x, y, z in zip(*out):
+        assert torch.equal(x, y) and torch.equal(x, z)
+    assert not torch.equal(out[0][1], k0) and not torch.equal(out[0][2], v0)
+    assert torch.equal(out[0][2], v)
+    for x, y, name in zip(out[0][:2], (q, k), "qk"):
+        x, y = x.float(), y.float()
+        assert torch.all((x - y).abs() <= 2.0 ** -7 * y.abs() + 1e-6), name
         # a result that falls halfway between two bf16 numbers once it is a float (one in 2^16) may go either way
-        assert norm or name == "v" and np.array_equal(a, b) or np.mean(a != b) <= 2.0 ** -13, (name, np.mean(a != b))
+        assert norm or (x != y).float().mean() <= 2.0 ** -13, (name, (x != y).float().mean())
 
 
 @pytest.mark.parametrize("M,H", [(1, 8), (6, 248), (6, 256), (3, 504), (5, 512), (4, 520), (33, 2048), (7, 2056), (9, 4096), (2, 4104), (6, 8192), (3, 8200), (5, 77)])
