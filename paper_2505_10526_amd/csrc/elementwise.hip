@@ -624,9 +624,16 @@ extern "C" int massv_rope_append(const massv_attn_desc* desc, const void* qkv, c
     const int64_t M = (int64_t)a.batch * a.n_query;
     if (M > 0x7fffffff || a.n_q_heads + 2 * a.n_kv_heads > 65535) return MASSV_EUNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
+    // bf16 by cache blocks where there are enough rows to pay for a workgroup's own sines (8 a thread, 3 us) and enough of
+    // them in a block of 32.  Measured over 1 to 5000 rows, kernel by rows against by blocks: 28 / 4 heads of 128, 16 x 16 rows
+    // 7.2 and 7.8 us, 16 x 24 8.5 and 7.9, 1 x 100 4.0 and 5.9; 12 / 2 heads, 16 x 31 rows 5.7 and 6.1, 8 x 100 7.7 and 7.4;
+    // 16 / 8 heads of 256, 8 x 14 rows 6.5 and 8.2, 8 x 24 8.7 and 8.4; 40 / 8 heads of 64, 8 x 28 rows 6.7 and 7.8, 16 x 20
+    // 9.3 and 7.5; 64 x 8 rows 25.0 and 23.2 at best, 64 x 2 4.6 and 25.7.
     const int n_blk = (a.n_query + MASSV_V_BLOCK - 1) / MASSV_V_BLOCK + 1;      // cache blocks that L_q rows can touch
-    // (a launch has fewer than 2^32 threads, and a grid fewer than 2^31 workgroups in x)
-    if (a.dtype == MASSV_BF16 && (int64_t)a.batch * n_blk * ((a.n_q_heads + a.n_kv_heads + 1) / 2 + a.n_kv_heads) * 2 * a.head_dim <= 0xffffffffll) {
+    const int64_t head_rows = M * (a.n_q_heads + 2 * a.n_kv_heads);
+    // (a launch has fewer than 2^32 threads)
+    if (a.dtype == MASSV_BF16 && a.n_query >= 20 && head_rows >= (a.head_dim == 64 ? 16384 : a.head_dim == 128 ? 12288 : 6144) &&
+        (int64_t)a.batch * n_blk * ((a.n_q_heads + a.n_kv_heads + 1) / 2 + a.n_kv_heads) * 2 * a.head_dim <= 0xffffffffll) {
         // rotary heads per workgroup: the more, the fewer times an angle is worked out; at least two workgroups per
         // compute unit before that counts
         int heads_per = 8;
