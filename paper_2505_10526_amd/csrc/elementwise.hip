@@ -273,7 +273,7 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
     const size_t m = (size_t)b * Lq + (live ? i : 0);
     const bf16_t* src = qkv + m * width + j;
     if ((int)blockIdx.y >= rotary_groups) {
-        __shared__ bf16_t vt[MASSV_V_BLOCK][D + 8];
+        __shared__ __align__(16) bf16_t vt[MASSV_V_BLOCK][D + 8];      // written 16 bytes at a time
         const int g = blockIdx.y - rotary_groups;
         if (live) {
             const bf16_t* vs = src + (size_t)(rotary + g) * D;
