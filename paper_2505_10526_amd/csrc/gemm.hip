@@ -43,6 +43,7 @@
 
 #include <limits.h>
 #include <atomic>
+#include <type_traits>
 
 namespace massv {
 
@@ -456,48 +457,56 @@ __device__ inline float4 scale_by(float4 a, float4 b) { return make_float4(a.x *
 
 // acc[i][r] = sum_k w[i][k] g[k] x[m0 + r][k] / rms(x[m0 + r]) (NORM), or without g and rms; every lane gets the sums.
 // Rows past M repeat the last one.  K % VEC == 0.
-template <int VEC, int NW, bool NORM>
+template <int VEC, int NW, bool NORM, int R>
 __device__ inline void rows_dot(const float* __restrict__ x, const float* const (&w)[NW], const float* __restrict__ g, float eps,
-                                int m0, int M, int K, float (&acc)[NW][kF32Rows]) {
+                                int m0, int M, int K, float (&acc)[NW][R]) {
     typedef typename FVec<VEC>::type V;
     const int lane = threadIdx.x, kv = K / VEC;
-    const V* xr[kF32Rows];
-    float ss[kF32Rows];
+    const V* xr[R];
+    float ss[R];
 #pragma unroll
-    for (int r = 0; r < kF32Rows; ++r) {
+    for (int r = 0; r < R; ++r) {
         xr[r] = reinterpret_cast<const V*>(x + (size_t)(m0 + r < M ? m0 + r : M - 1) * K);
         ss[r] = 0.f;
 #pragma unroll
         for (int i = 0; i < NW; ++i) acc[i][r] = 0.f;
     }
-    for (int k0 = 0; k0 < kv; k0 += 4 * kWave) {       // four steps' loads in flight; a step past K counts as zeros
-        V xv[4][kF32Rows], wv[4][NW], gv[4];
+    // S steps of kWave groups with all their loads in flight: four at a time, then what is left (four
+    // every time, zeros past K: 48 x 64 -> 4096 51 us, 15 without them)
+    auto steps = [&](int k0, auto count) {
+        constexpr int S = decltype(count)::value;
+        V xv[S][R], wv[S][NW], gv[S];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < S; ++u) {
             const int k = k0 + u * kWave + lane;
             const bool ok = k < kv;
 #pragma unroll
             for (int i = 0; i < NW; ++i) wv[u][i] = ok ? reinterpret_cast<const V*>(w[i])[k] : V{};
             if constexpr (NORM) gv[u] = ok ? reinterpret_cast<const V*>(g)[k] : V{};
 #pragma unroll
-            for (int r = 0; r < kF32Rows; ++r) xv[u][r] = ok ? xr[r][k] : V{};
+            for (int r = 0; r < R; ++r) xv[u][r] = ok ? xr[r][k] : V{};
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < S; ++u) {
             if constexpr (NORM) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) wv[u][i] = scale_by(wv[u][i], gv[u]);
 #pragma unroll
-                for (int r = 0; r < kF32Rows; ++r) ss[r] = dot_step(xv[u][r], xv[u][r], ss[r]);
+                for (int r = 0; r < R; ++r) ss[r] = dot_step(xv[u][r], xv[u][r], ss[r]);
             }
 #pragma unroll
             for (int i = 0; i < NW; ++i)
 #pragma unroll
-                for (int r = 0; r < kF32Rows; ++r) acc[i][r] = dot_step(wv[u][i], xv[u][r], acc[i][r]);
+                for (int r = 0; r < R; ++r) acc[i][r] = dot_step(wv[u][i], xv[u][r], acc[i][r]);
         }
-    }
+    };
+    int k0 = 0;
+    for (; k0 + 3 * kWave < kv; k0 += 4 * kWave) steps(k0, std::integral_constant<int, 4>{});
+    if (k0 + 2 * kWave < kv) steps(k0, std::integral_constant<int, 3>{});
+    else if (k0 + kWave < kv) steps(k0, std::integral_constant<int, 2>{});
+    else if (k0 < kv) steps(k0, std::integral_constant<int, 1>{});
 #pragma unroll
-    for (int r = 0; r < kF32Rows; ++r) {
+    for (int r = 0; r < R; ++r) {
         float rstd = 1.f;
         if constexpr (NORM) rstd = 1.0f / sqrtf(wave_sum(ss[r]) / (float)K + eps);
 #pragma unroll
@@ -505,21 +514,21 @@ __device__ inline void rows_dot(const float* __restrict__ x, const float* const 
     }
 }
 
-// One feature per wave: y = x w^T (+ bias) (+ residual); up to three matrices side by side.
+// One feature per wave and R rows: y = x w^T (+ bias) (+ residual); up to three matrices side by side.
 struct F32Mats { const float* w[3]; const float* bias[3]; int n[3]; };
-template <int VEC, bool NORM>
+template <int VEC, bool NORM, int R>
 __global__ __launch_bounds__(kWave)
 void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ g, float eps, F32Mats mats, const float* residual,
                      float* y, int M, int K, int ldy) {
-    const int n = blockIdx.x, m0 = blockIdx.y * kF32Rows, lane = threadIdx.x;
+    const int n = blockIdx.x, m0 = blockIdx.y * R, lane = threadIdx.x;
     int seg = 0, local = n;
     if (local >= mats.n[0]) { local -= mats.n[0]; seg = 1; if (local >= mats.n[1]) { local -= mats.n[1]; seg = 2; } }
     const float* const w[1] = {mats.w[seg] + (size_t)local * K};
-    float acc[1][kF32Rows];
-    rows_dot<VEC, 1, NORM>(x, w, g, eps, m0, M, K, acc);
+    float acc[1][R];
+    rows_dot<VEC, 1, NORM, R>(x, w, g, eps, m0, M, K, acc);
     const float b = mats.bias[seg] ? mats.bias[seg][local] : 0.f;
 #pragma unroll
-    for (int r = 0; r < kF32Rows; ++r)
+    for (int r = 0; r < R; ++r)
         if (lane == r && m0 + r < M) {
             const size_t o = (size_t)(m0 + r) * ldy + n;
             y[o] = acc[0][r] + b + (residual ? residual[o] : 0.f);
@@ -534,7 +543,7 @@ void gated_f32_kernel(const float* __restrict__ x, const float* __restrict__ g, 
     const int f = blockIdx.x, m0 = blockIdx.y * kF32Rows, lane = threadIdx.x;
     const float* const w[2] = {wg + (size_t)f * K, wu + (size_t)f * K};
     float acc[2][kF32Rows];
-    rows_dot<VEC, 2, NORM>(x, w, g, eps, m0, M, K, acc);
+    rows_dot<VEC, 2, NORM, kF32Rows>(x, w, g, eps, m0, M, K, acc);
     float gv = acc[0][0], uv = acc[1][0];
 #pragma unroll
     for (int r = 1; r < kF32Rows; ++r)
@@ -561,7 +570,7 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     const size_t row0 = (size_t)hl * d + j;
     const float* const w[2] = {mats.w[seg] + row0 * K, mats.w[seg] + (row0 + half) * K};
     float acc[2][kF32Rows];
-    rows_dot<VEC, 2, true>(x, w, g, eps, m0, M, K, acc);
+    rows_dot<VEC, 2, true, kF32Rows>(x, w, g, eps, m0, M, K, acc);
     float x1 = acc[0][0], x2 = acc[1][0];
 #pragma unroll
     for (int r = 1; r < kF32Rows; ++r)
@@ -592,9 +601,10 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     }
 }
 
-// 16-byte loads need K in whole groups of four and rows that start at a multiple of 16 bytes.
+// 16-byte loads need K in whole groups of four and rows that start at a multiple of 16 bytes.  Under 256 values a row they
+// leave lanes without work: 64 -> 4096 at 64 rows 18 us with single values, 29 with 16 bytes; 128 -> 152064 at 8 rows 71 and 133.
 static bool f32_wide(const void* a, const void* b, const void* c, const void* d, const void* e, int K) {
-    return K % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d | (uintptr_t)e) % 16) == 0;
+    return K % 4 == 0 && K >= 4 * kWave && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d | (uintptr_t)e) % 16) == 0;
 }
 
 int launch_qkv_rope_f32(const GemmArgs& g, const int32_t* pos, const int32_t* kv_len, void* q_out, void* k_cache, void* v_cache,
@@ -607,6 +617,11 @@ int launch_qkv_rope_f32(const GemmArgs& g, const int32_t* pos, const int32_t* kv
                   (float*)q_out, (float*)k_cache, (float*)v_cache, g.M, g.K, a.n_query, a.n_q_heads, a.n_kv_heads, a.head_dim,
                   a.l_max, log2((double)theta));
     return launch_status();
+}
+
+template <int R>
+static auto gemm_f32_pick(bool norm, bool wide) {
+    return norm ? (wide ? gemm_f32_kernel<4, true, R> : gemm_f32_kernel<1, true, R>) : (wide ? gemm_f32_kernel<4, false, R> : gemm_f32_kernel<1, false, R>);
 }
 
 static int launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
@@ -624,8 +639,8 @@ static int launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
     }
     const int N = g.n[0] + g.n[1] + g.n[2];
     const float* res = g.epilogue == EPI_RESIDUAL ? (const float*)g.residual : nullptr;
-    const auto kernel = gain ? (wide ? gemm_f32_kernel<4, true> : gemm_f32_kernel<1, true>)
-                             : (wide ? gemm_f32_kernel<4, false> : gemm_f32_kernel<1, false>);
+    // few rows: a wave does not multiply rows that are not there (1 x 256 -> 152064 34 us, 81 as one of 8 rows)
+    const auto kernel = g.M == 1 ? gemm_f32_pick<1>(gain, wide) : g.M == 2 ? gemm_f32_pick<2>(gain, wide) : g.M <= 4 ? gemm_f32_pick<4>(gain, wide) : gemm_f32_pick<8>(gain, wide);
     hipLaunchKernelGGL(kernel, dim3(N, row_groups), dim3(kWave), 0, st, x, gain, g.norm_eps, mats, res, (float*)g.y, g.M, g.K, N);
     return launch_status();
 }

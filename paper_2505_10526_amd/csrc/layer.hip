@@ -219,6 +219,13 @@ extern "C" int massv_lm_head_logits(const void* x, const void* final_norm, const
     if (dtype == MASSV_BF16) {                  // normalise (or only re-lay out) into operand order
         if ((rc = launch_rmsnorm_packed(x, final_norm, workspace, M, H, norm_eps, st)) != MASSV_OK) return rc;
         g.x = workspace;
+    } else if (final_norm && (V > 4096 || (H < 512 && (M > 8 || H <= 64)))) {
+        // a wave per feature and 8 rows would form the rows' norms V ceil(M / 8) times over, which only pays for the launch it
+        // saves while features are few, and products long or rows few (norm apart and in the product: V = 4096, H = 64, 48
+        // rows 19 and 42 us, 6 rows 6.8 and 8.1; H = 256, 48 rows 38 and 42, 6 rows 12.6 and 8.2; H = 512, 48 rows 58 and 46;
+        // V = 32003, H = 256, 8 rows 42 and 56)
+        if ((rc = massv_rmsnorm(x, final_norm, workspace, M, H, norm_eps, MASSV_F32, stream)) != MASSV_OK) return rc;
+        g.x = workspace;
     } else {                                    // the projection normalises its rows itself
         g.norm = final_norm; g.norm_eps = norm_eps;
     }

@@ -498,3 +498,22 @@ def test_vocabulary_statistics_carried_across_shares_keep_small_terms():
     want = n0 + (V - n0) * np.exp(-17.25)
     assert abs(rec["s"].sum() / want - 1) <= 2e-6 * 2.9e-7 + 1e-12
     assert torch.equal(logits[0], w[:, 0].float())
+
+
+@pytest.mark.parametrize("H", [7, 64, 68, 252, 256, 260, 512, 700, 1028])
+@pytest.mark.parametrize("M,V", [(1, 100), (2, 4097), (3, 33), (4, 5000), (5, 70), (8, 4096), (9, 4100), (17, 64)])
+def test_fp32_logits_rows_and_widths(M, V, H):
+    """1, 2, 4 or 8 rows a wave, single or 16-byte loads with one to four steps in flight, the norm in the product or ahead
+    of it, against float64; the bound is the order of fp32 sums of H products (sqrt(H) roundings of 2^-24, four times)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * H + V)
+    x, w = torch.randn(M, H, generator=g, device="cuda"), torch.randn(V, H, generator=g, device="cuda")
+    gain = 1 + 0.1 * torch.randn(H, generator=g, device="cuda")
+    for norm in (None, gain):
+        got = binding.lm_head_logits(x, norm, w, 1e-6)
+        y = x.double()
+        if norm is not None:
+            y = y / (y.square().mean(-1, keepdim=True) + 1e-6).sqrt() * norm.double()
+        ref = y @ w.double().T
+        err = (got.double() - ref).abs().max() / ref.abs().max()
+        assert err <= 4 * H ** 0.5 * 2.0 ** -24, (norm is not None, err)
