@@ -88,8 +88,8 @@ void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__
             if constexpr (VEC == 4) {
 #pragma unroll 16
                 for (int k = 0; k < d; k += 4) {
-                    const float4 kv = *reinterpret_cast<const float4*>(kr + k), qv = *reinterpret_cast<const float4*>(qs + k);
-                    dot = fmaf(qv.w, kv.w, fmaf(qv.z, kv.z, fmaf(qv.y, kv.y, fmaf(qv.x, kv.x, dot))));
+                    const floatx4 kv = *reinterpret_cast<const floatx4_any*>(kr + k), qv = *reinterpret_cast<const floatx4*>(qs + k);
+                    dot = fmaf(qv[3], kv[3], fmaf(qv[2], kv[2], fmaf(qv[1], kv[1], fmaf(qv[0], kv[0], dot))));
                 }
             } else {
                 for (int k = 0; k < d; ++k) dot += qs[k] * kr[k];
@@ -120,13 +120,13 @@ void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__
                 const float* vr = vc + v_index(bg, l_max, d, k0, c);
                 const float* wr = w + blk * kBlk;
                 if (VEC == 4 && k0 >= lo && k0 + kBlk <= n_vis) {
-                    float4 vv[kBlk / 4];
+                    floatx4 vv[kBlk / 4];
 #pragma unroll
-                    for (int t = 0; t < kBlk / 4; ++t) vv[t] = reinterpret_cast<const float4*>(vr)[t];
+                    for (int t = 0; t < kBlk / 4; ++t) vv[t] = reinterpret_cast<const floatx4_any*>(vr)[t];
 #pragma unroll
                     for (int t = 0; t < kBlk / 4; ++t) {
-                        const float4 wv = reinterpret_cast<const float4*>(wr)[t];
-                        acc = fmaf(wv.w, vv[t].w, fmaf(wv.z, vv[t].z, fmaf(wv.y, vv[t].y, fmaf(wv.x, vv[t].x, acc))));
+                        const floatx4 wv = reinterpret_cast<const floatx4*>(wr)[t];
+                        acc = fmaf(wv[3], vv[t][3], fmaf(wv[2], vv[t][2], fmaf(wv[1], vv[t][1], fmaf(wv[0], vv[t][0], acc))));
                     }
                 } else {
                     const int t0 = lo > k0 ? lo - k0 : 0, t1 = n_vis - k0 < kBlk ? n_vis - k0 : kBlk;
@@ -613,8 +613,7 @@ int launch_attention(const massv_attn_desc& a, const void* q, const void* k_cach
                      const int32_t* kv_len, void* out, void* ws, bool out_packed, hipStream_t st) {
     const float scale = a.scale > 0.f ? a.scale : 1.0f / sqrtf((float)a.head_dim);
     if (a.dtype == MASSV_F32) {
-        const bool wide = a.head_dim % 4 == 0 && (((uintptr_t)k_cache | (uintptr_t)v_cache) % 16) == 0;      // 16-byte loads
-        hipLaunchKernelGGL(wide ? attention_f32_kernel<4> : attention_f32_kernel<1>, dim3(a.n_query, a.n_q_heads, a.batch), dim3(256), 0, st,
+        hipLaunchKernelGGL(a.head_dim % 4 == 0 ? attention_f32_kernel<4> : attention_f32_kernel<1>, dim3(a.n_query, a.n_q_heads, a.batch), dim3(256), 0, st,
                            (const float*)q, (const float*)k_cache, (const float*)v_cache, kv_len, (float*)out,
                            a.n_query, a.n_q_heads, a.n_kv_heads, a.head_dim, a.l_max, scale, a.window);
         return launch_status();

@@ -16,6 +16,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_any __attribute__((ext_vector_type(8), aligned(2)));      // 16 bytes in one access, from any address
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));      // 16 bytes in one access, from any float on
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Status of the launch that was just enqueued.

@@ -448,12 +448,11 @@ const float before = best_v[mt];
 // ---------------------------------------------------------------------------
 constexpr int kF32Rows = 8;
 
-template <int VEC> struct FVec { typedef float4 type; };
+template <int VEC> struct FVec { typedef floatx4_any type; };
 template <> struct FVec<1> { typedef float type; };
 __device__ inline float dot_step(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ inline float dot_step(float4 a, float4 b, float c) { return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, fmaf(a.x, b.x, c)))); }
-__device__ inline float scale_by(float a, float b) { return a * b; }
-__device__ inline float4 scale_by(float4 a, float4 b) { return make_float4(a.x * b.x, a.y * b.y, a.z * b.z, a.w * b.w); }
+__device__ inline float dot_step(floatx4_any a, floatx4_any b, float c) { return fmaf(a[3], b[3], fmaf(a[2], b[2], fmaf(a[1], b[1], fmaf(a[0], b[0], c)))); }
+template <typename V> __device__ inline V scale_by(V a, V b) { return a * b; }
 
 // acc[i][r] = sum_k w[i][k] g[k] x[m0 + r][k] / rms(x[m0 + r]) (NORM), or without g and rms; every lane gets the sums.
 // Rows past M repeat the last one.  K % VEC == 0.
@@ -601,18 +600,17 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     }
 }
 
-// 16-byte loads need K in whole groups of four and rows that start at a multiple of 16 bytes.  Under 256 values a row they
-// leave lanes without work: 64 -> 4096 at 64 rows 18 us with single values, 29 with 16 bytes; 128 -> 152064 at 8 rows 71 and 133.
-static bool f32_wide(const void* a, const void* b, const void* c, const void* d, const void* e, int K) {
-    return K % 4 == 0 && K >= 4 * kWave && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d | (uintptr_t)e) % 16) == 0;
-}
+// 16-byte loads need K in whole groups of four (rows may start at any float: which loads are used, and with them the order of
+// the sums, depends on K alone).  Under 256 values a row they leave lanes without work: 64 -> 4096 at 64 rows 18 us with single
+// values, 29 with 16 bytes; 128 -> 152064 at 8 rows 71 and 133.
+static bool f32_wide(int K) { return K % 4 == 0 && K >= 4 * kWave; }
 
 int launch_qkv_rope_f32(const GemmArgs& g, const int32_t* pos, const int32_t* kv_len, void* q_out, void* k_cache, void* v_cache,
                         const massv_attn_desc& a, float theta, hipStream_t st) {
     F32Mats mats;
     for (int s = 0; s < 3; ++s) { mats.w[s] = (const float*)g.w[s]; mats.bias[s] = (const float*)g.bias[s]; mats.n[s] = g.n[s]; }
     const dim3 grid((a.n_q_heads + 2 * a.n_kv_heads) * (a.head_dim / 2), (g.M + kF32Rows - 1) / kF32Rows);
-    const auto kernel = f32_wide(g.x, g.w[0], g.w[1], g.w[2], g.norm, g.K) ? qkv_rope_f32_kernel<4> : qkv_rope_f32_kernel<1>;
+    const auto kernel = f32_wide(g.K) ? qkv_rope_f32_kernel<4> : qkv_rope_f32_kernel<1>;
     hipLaunchKernelGGL(kernel, grid, dim3(kWave), 0, st, (const float*)g.x, (const float*)g.norm, g.norm_eps, mats, pos, kv_len,
                   (float*)q_out, (float*)k_cache, (float*)v_cache, g.M, g.K, a.n_query, a.n_q_heads, a.n_kv_heads, a.head_dim,
                   a.l_max, log2((double)theta));
@@ -627,7 +625,7 @@ static auto gemm_f32_pick(bool norm, bool wide) {
 static int launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
     F32Mats mats;
     for (int s = 0; s < 3; ++s) { mats.w[s] = (const float*)g.w[s]; mats.bias[s] = (const float*)g.bias[s]; mats.n[s] = g.n[s]; }
-    const bool wide = f32_wide(g.x, g.w[0], g.n[1] ? g.w[1] : nullptr, g.n[2] ? g.w[2] : nullptr, g.norm, g.K);
+    const bool wide = f32_wide(g.K);
     const unsigned row_groups = (g.M + kF32Rows - 1) / kF32Rows;
     const float *x = (const float*)g.x, *gain = (const float*)g.norm;
     if (g.epilogue == EPI_GATED) {

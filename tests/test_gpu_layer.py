@@ -430,13 +430,14 @@ def test_fp32_layer_widths(s, B, Q):
 
 def test_fp32_layer_many_keys_and_unaligned_rows():
     """More keys than one tile of 256, and every operand one float off a multiple of 16 bytes (a slice of a larger
-    buffer): the same numbers as the 16-byte path."""
+    buffer): the same bits."""
     s, B, Q, seed = synth.TINY, 2, 6, 45
     w = synth.layer_weights(s, seed, std=0.05)
     kv = synth.kv_cache(s, B, Q, [900, 513], [64, 30], seed, hot_keys=2)
     x, pos = synth.hidden_states(s, B, Q, seed), synth.positions(kv.kv_len, kv.n_img, Q)
     y_ref, _, _ = O.verify_layer(s, w, x, pos, kv.k, kv.v, kv.kv_len)
     lm = round_up(kv.l_max, 32)
+    got = []
     for off in (0, 1):
         def put(a):
             t = to_dev(a, "f32")
@@ -450,6 +451,10 @@ def test_fp32_layer_many_keys_and_unaligned_rows():
         binding.verify_layer(cfg_of(s), {k: (None if v is None else put(v)) for k, v in w.items()}, xd, i32(pos), kd, vd, i32(kv.kv_len))
         torch.cuda.synchronize()
         assert_close(xd.cpu().numpy(), y_ref, TOL_F32, f"offset {off}")
+        got.append((xd, kd, vd))
+    assert torch.equal(got[0][0], got[1][0])
+    for a, b in zip(got[0][1:], got[1][1:]):                          # caches: bits, NaN in rows past the end
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
 
 
 @pytest.mark.parametrize("M,H,V", [(1, 32, 40976), (16, 64, 65600), (17, 96, 45072), (33, 544, 82000), (48, 512, 40960), (64, 160, 20512), (49, 32, 70000)])
