@@ -258,11 +258,15 @@ void gemm_stream_kernel(GemmDev g) {
 // workgroup's shares side by side instead the logits took 203 us.
 // EPI_ARGMAX and EPI_LOGITS_STATS carry a lane's maximum (and sum) across the workgroup's shares: one record per row and
 // workgroup.
+// MANY: more than one share a workgroup (with the loop over shares compiled in, single ones took up to 9 % longer: 16 rows, 1024
+// -> 50000 21.2 us, 19.3 without).  Plain logits of one share a workgroup and more workgroups than CUs are gemm_stream_kernel's
+// (32 rows, 1024 -> 45056 19.6 us, 21.7 here; 1024 -> 8192 7.6 there and 7.5 here).
 // ---------------------------------------------------------------------------
-template <int MT, int NT, int EPI>
+template <int MT, int NT, int EPI, bool MANY>
 __global__ __launch_bounds__(kGemmWaves * kWave)
 void gemm_vocab_kernel(GemmDev g) {
     constexpr int WK = kGemmWaves;
+    const int shares = MANY ? g.rounds : 1;
     extern __shared__ floatx4 red[];                 // [WK][GRP*MT][64]
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int lr = lane % 16, lc = lane / 16;
@@ -328,7 +332,7 @@ void gemm_vocab_kernel(GemmDev g) {
     // Barrier for what travels through LDS; loads on their way into registers stay on their way.
     auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     int par = 0;
-    for (int round = 0; round < g.rounds; ++round) {
+    for (int round = 0; round < shares; ++round) {
         const int first = unit0, owned = n_units < g.tiles[0] - unit0 ? n_units : g.tiles[0] - unit0;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
@@ -337,7 +341,7 @@ void gemm_vocab_kernel(GemmDev g) {
         for (int it = 0; it < n_it; ++it, par ^= 1) {
             bool more = it + 1 < n_it;
             int nx = k0_of(it + 1), ncnt = cnt_of(it + 1);
-            if (!more && round + 1 < g.rounds) {
+            if (MANY && !more && round + 1 < shares) {
                 take_share((round + 1) * gridDim.x + blockIdx.x);
                 more = true; nx = k0_of(0); ncnt = cnt_of(0);
             }
@@ -353,12 +357,12 @@ void gemm_vocab_kernel(GemmDev g) {
                 if (more) wload(nt, nx, ncnt);            // refill this tile's slot for the wave's next four steps
             }
         }
-        if (n_it == 0 && round + 1 < g.rounds) take_share((round + 1) * gridDim.x + blockIdx.x);      // a wave without a step (tiny K)
+        if (MANY && n_it == 0 && round + 1 < shares) take_share((round + 1) * gridDim.x + blockIdx.x);      // a wave without a step (tiny K)
 
         // ---- sum the waves through LDS in wave order, GRP tiles per round ----
         constexpr int GRP = ReduceGroup<MT, NT>::value;
         for (int g0 = 0; g0 < NT; g0 += GRP) {
-            if (g0 || round) lds_barrier();
+            if (g0 || (MANY && round)) lds_barrier();
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
                 if (nt >= g0 && nt < g0 + GRP)
@@ -722,20 +726,28 @@ GemmPlan gemm_plan(const GemmArgs& g) {
     return best;
 }
 
+constexpr bool is_vocab(int epi) { return epi == EPI_LOGITS || epi == EPI_ARGMAX || epi == EPI_LOGITS_STATS; }
+
 // Shares that one workgroup of the vocabulary projection works off: all rounds of one workgroup per CU, where they are
-// full.  Up to three rounds of 16 rows and plain logits stay a workgroup per share: two of those small workgroups fit a
-// CU and cover each other (4 rows, 1536 -> 100000: 47.7 us, 51.1 as one workgroup; at four rounds, 8 rows, -> 152064,
-// 80.1 against 75.3).
-static int gemm_rounds(const GemmPlan& p, int M, int epilogue) {
-    if (epilogue != EPI_LOGITS && epilogue != EPI_ARGMAX && epilogue != EPI_LOGITS_STATS) return 1;
+// full.  Plain logits of few rows stay a workgroup per share where two such workgroups fit a CU and cover each other (16 rows
+// and 8 tile slots, 32 and 4), or where the shares leave slots empty and so have less to cover.  Measured, a workgroup per
+// share and one per CU: 16 rows, 8 slots, 1024 -> 45056 17.0 and 18.3 us, 2048 -> 65536 43.2 and 43.9, 640 -> 262144 63.1 and
+// 63.6; 10 slots, 8.1 tiles, 1536 -> 100000 52.2 and 53.7, 8.5 tiles, 1536 -> 70000 39.0 and 37.5, 9.3, 1536 -> 152064 83.0 and
+// 79.6; 32 rows, 4 slots, 2048 -> 49152 37.3 and 39.3, 8.1 of 10 tiles, 5120 -> 100352 181 and 184, 6.1 of 8, 1024 -> 50000
+// 24.7 and 22.2, 7.5 of 8, 2048 -> 92544 72.4 and 68.3; from 33 rows on one per CU gains 3 to 33 %.
+static int gemm_rounds(const GemmPlan& p, const GemmArgs& g) {
+    if (!is_vocab(g.epilogue)) return 1;
     if (p.groups <= kCUs || p.groups % kCUs) return 1;
-    const int rounds = p.groups / kCUs;
-    return epilogue == EPI_LOGITS && M <= 16 && rounds < 4 ? 1 : rounds;
+    if (g.epilogue == EPI_LOGITS && g.M <= 32) {
+        const bool filled = g.n[0] / 16 >= 0.84 * p.groups * p.nt;
+        if (g.M <= 16 ? !(p.nt == 10 && filled) : p.nt == 4 || !(filled || g.K <= 1024)) return 1;
+    }
+    return p.groups / kCUs;
 }
 
 int gemm_row_pieces(const GemmArgs& g) {
     const GemmPlan p = gemm_plan(g);
-    return p.groups / gemm_rounds(p, g.M, g.epilogue);
+    return p.groups / gemm_rounds(p, g);
 }
 
 size_t gemm_partial_bytes(const GemmArgs& g) {
@@ -744,14 +756,15 @@ size_t gemm_partial_bytes(const GemmArgs& g) {
     return (size_t)p.slabs * ((g.M + 15) / 16 * 16) * n_total(g) * sizeof(float);
 }
 
-template <int MT, int NT, int EPI>
+enum StreamKind { STREAM, VOCAB_ONE, VOCAB_MANY };
+template <int MT, int NT, int EPI, int KIND>
 static constexpr auto stream_kernel() {
-    if constexpr (EPI == EPI_LOGITS || EPI == EPI_ARGMAX || EPI == EPI_LOGITS_STATS) return &gemm_vocab_kernel<MT, NT, EPI>;
-    else return &gemm_stream_kernel<MT, NT, EPI>;
+    if constexpr (KIND == STREAM) return &gemm_stream_kernel<MT, NT, EPI>;
+    else return &gemm_vocab_kernel<MT, NT, EPI, KIND == VOCAB_MANY>;
 }
 
-template <int MT, int NT, int EPI>
-static int launch_stream(const GemmDev& d, const GemmPlan& p, int kid, hipStream_t st) {
+template <int MT, int NT, int EPI, int KIND>
+static int launch_stream_as(const GemmDev& d, const GemmPlan& p, int kid, hipStream_t st) {
     constexpr int GRP = ReduceGroup<MT, NT>::value;
     const size_t lds = (size_t)kGemmWaves * GRP * MT * kWave * sizeof(floatx4);
     if (lds > 48 * 1024) {                       // more dynamic LDS than a kernel may use by default
@@ -759,14 +772,24 @@ static int launch_stream(const GemmDev& d, const GemmPlan& p, int kid, hipStream
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MASSV_ELAUNCH;
         if (!ready[dev].load(std::memory_order_acquire)) {
-            if (hipFuncSetAttribute((const void*)stream_kernel<MT, NT, EPI>(), hipFuncAttributeMaxDynamicSharedMemorySize,
+            if (hipFuncSetAttribute((const void*)stream_kernel<MT, NT, EPI, KIND>(), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds) != hipSuccess) return MASSV_ELAUNCH;
             ready[dev].store(true, std::memory_order_release);
         }
     }
     const dim3 grid = (EPI == EPI_PARTIAL) ? dim3(p.slabs, p.groups) : dim3(p.groups / d.rounds, p.slabs);
-    launch_traced(kid, stream_kernel<MT, NT, EPI>(), grid, dim3(kGemmWaves * kWave), lds, st, d);
+    launch_traced(kid, stream_kernel<MT, NT, EPI, KIND>(), grid, dim3(kGemmWaves * kWave), lds, st, d);
     return MASSV_OK;
+}
+
+template <int MT, int NT, int EPI>
+static int launch_stream(const GemmDev& d, const GemmPlan& p, int kid, hipStream_t st) {
+    if constexpr (is_vocab(EPI)) {
+        if (d.rounds > 1) return launch_stream_as<MT, NT, EPI, VOCAB_MANY>(d, p, kid, st);
+        if (EPI != EPI_LOGITS || p.groups <= kCUs) return launch_stream_as<MT, NT, EPI, VOCAB_ONE>(d, p, kid, st);
+    }
+    if constexpr (!is_vocab(EPI) || EPI == EPI_LOGITS) return launch_stream_as<MT, NT, EPI, STREAM>(d, p, kid, st);
+    return MASSV_EUNSUPPORTED;                    // (not reached)
 }
 
 template <int MT, int EPI>
@@ -810,7 +833,7 @@ int launch_gemm(const GemmArgs& g, hipStream_t st) {
     {
         const int ut = (g.epilogue == EPI_GATED) ? 2 : 1;
         const int units = ((g.epilogue == EPI_GATED) ? 2 * d.tiles[0] : N / 16) / ut;
-        d.rounds = gemm_rounds(p, g.M, g.epilogue);
+        d.rounds = gemm_rounds(p, g);
         d.unit_base = units / p.groups;
         d.unit_rem = units % p.groups;
         if ((d.unit_base + (d.unit_rem ? 1 : 0)) * ut > p.nt) return MASSV_EUNSUPPORTED;     // cannot happen with gemm_plan's groups
