@@ -716,13 +716,19 @@ extern "C" int massv_prefill_attention(const massv_attn_desc* desc, const void* 
     p.Lq = a.n_query; p.n_q = a.n_q_heads; p.n_kv = a.n_kv_heads; p.l_max = a.l_max; p.window = a.window;
     p.n_tiles = 0;
     p.scale_log2 = scale * 1.4426950408889634f;
-    // d <= 128: 64 rows per wave and everything in registers is the faster kernel as soon as its workgroups of 256 rows
-    // fill the chip (28 / 4 heads, d = 128, 8 x 2048 positions 291 us, 367 with the other; 4 x 1111 ragged, 496 workgroups,
-    // 51 and 66).  Below that the length of one wave's loop counts, and 32 rows per wave have the shorter one (1 x 1111
-    // positions, 124 workgroups, 37.5 and 29.5; 1 x 2000, 220 workgroups, 64 and 51; 2 x 1111, 248 workgroups, 40 and 36).
-    const int64_t wide_wgs = (int64_t)a.batch * a.n_kv_heads *
-                             (((int64_t)a.n_query * (a.n_q_heads / a.n_kv_heads) + kPfWaves * 64 - 1) / (kPfWaves * 64));
-    const bool few = wide_wgs <= 256;
+    // d <= 128: a launch of 32 rows per wave that fits the chip (256 workgroups of 128 rows) is the faster one, by 1.16 to
+    // 1.65 over 300 calls: the length of one wave's loop counts there.  Larger ones take 64 rows per wave, with two exceptions.
+    // At d = 64 the smaller kernel stays ahead (1.05 to 1.5; its blocks are half as long) while workgroups of 256 rows would
+    // fit the chip, unless a window makes them all alike (0.96 to 1.3) or rows are few before a long cache (100 rows on
+    // 6000: 0.95).  At d = 128 it does so for long fresh prompts alone (24 tiles of 128 rows a pair and more, 224 workgroups
+    // of 256 in all; 1 x 2000, 28 / 4 heads: 64 and 51 us), whose many short key ranges fill up what the long ones leave:
+    // with a cache as long as the prompt 110 and 119 us, with window 512 30.5 and 43.
+    const int64_t pairs = (int64_t)a.batch * a.n_kv_heads, rows = (int64_t)a.n_query * (a.n_q_heads / a.n_kv_heads);
+    const int64_t wide = pairs * ((rows + kPfWaves * 64 - 1) / (kPfWaves * 64)), tiles = (rows + kPfWaves * 32 - 1) / (kPfWaves * 32);
+    const bool banded = a.window > 0 && a.window < a.l_max;
+    bool few = pairs * tiles <= 256;
+    if (a.head_dim == 64) few = few || (!banded && wide <= 256 && a.l_max / 8 <= a.n_query);
+    else few = few || (!banded && !n_bidir && wide <= 224 && tiles >= 24 && (int64_t)a.l_max * 4 <= (int64_t)a.n_query * 5 + 128);
     switch (a.head_dim) {
         case 64: return few ? launch_prefill_lds<64>(a, p, st) : launch_prefill<64, 2>(a, p, st);
         case 128: return few ? launch_prefill_lds<128>(a, p, st) : launch_prefill<128, 2>(a, p, st);

@@ -135,10 +135,13 @@ def test_rows_and_blocks_through_lds(heads, kv_len, n_new, window, bidir, d):
     run_case(s, kv_len, n_new, [t // 2 for t in total], seed=sum(total), window=window, bidir=bidir)
 
 
-@pytest.mark.parametrize("heads,n_new", [((1, 1), [512] * 129), ((7, 1), [293] * 32), ((7, 1), [293] * 33)])
-def test_both_sides_of_the_launch_size_rule(heads, n_new):
-    """258, 256 and 264 workgroups of 256 stacked rows: the kernel with 64 rows per wave above 256, the other up to it."""
-    s = synth.LayerShape(256, heads[0], heads[1], 64, 704, 4096, dtype="bf16")
+@pytest.mark.parametrize("d,heads,n_new", [
+    (64, (1, 1), [512] * 129), (64, (7, 1), [292] * 32), (64, (7, 1), [292] * 33),      # 258, 256 and 264 workgroups of 256 rows
+    (128, (1, 1), [128] * 256), (128, (1, 1), [128] * 257), (128, (1, 1), [129] * 200),      # 256, 257 and 400 of 128
+    (128, (8, 1), [384] * 11), (128, (8, 1), [368] * 12)])                              # 24 and 23 tiles of 128 rows a pair
+def test_both_sides_of_the_launch_size_rule(d, heads, n_new):
+    """Launches just inside and just outside the rules that choose between 32 and 64 rows per wave."""
+    s = synth.LayerShape(256, heads[0], heads[1], d, 704, 4096, dtype="bf16")
     run_case(s, [0] * len(n_new), n_new, [9] * len(n_new), seed=len(n_new), check=[0, len(n_new) - 1])
 
 
