@@ -359,6 +359,10 @@ void prefill_attention_kernel(PrefillParams p) {
 // exponentials of block i sit between the matrix instructions of block i + 1's scores, which are formed in two chains.
 // A value block's pieces (8 keys of a dim) lie in LDS at place c ^ (dim / 4) % 4 of the dim's four: the 32 dims of a
 // fragment are 64 bytes apart, which as they lie in the cache is four lanes to a bank.
+// Waves without rows only bring their share of the blocks in (as long as they multiplied the last row along, calls of up to 32
+// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 4 to 6 % faster: 16 / 8 heads, one row on
+// 100 cached 9.0 -> 10.2 -> 9.3 us).  What it does not win: ungrouped heads under a window, where the four waves'
+// blocks are the union of what each sees (4 / 4 heads, window 512, 80 rows 29.8 -> 30.9).
 // d = 256, 4 x 2000 positions, 16 / 8 heads: 252 -> 172 us (0.52 -> 0.76 PFLOP/s; refilling each operand set early, without LDS:
 // 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
 // ---------------------------------------------------------------------------
@@ -429,9 +433,24 @@ void prefill_attention_lds_kernel(PrefillParams p) {
         barrier();
         if (blk + 3 < blk_end) request(blk + 3);
     };
-    request(blk_begin);
-    if (blk_begin + 1 < blk_end) request(blk_begin + 1);
-    if (blk_begin + 2 < blk_end) request(blk_begin + 2);
+    // the first block and Q have to be there to start with
+    auto start = [&]() {
+        if (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else if (blk_begin + 2 < blk_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(4 * NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        barrier();
+    };
+    auto request_first = [&]() {
+        request(blk_begin);
+        if (blk_begin + 1 < blk_end) request(blk_begin + 1);
+        if (blk_begin + 2 < blk_end) request(blk_begin + 2);
+    };
+    if (r0 >= rows) {                              // a wave past the last row only brings its share of the blocks in
+        request_first();
+        start();
+        for (int blk = blk_begin; blk < blk_end; ++blk) open(blk);
+        return;
+    }
 
     bf16x8 qreg[KS];
     int hi_row, lo_row;
@@ -444,6 +463,7 @@ void prefill_attention_lds_kernel(PrefillParams p) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 16 + hh * 8);
     }
+    request_first();
 
     // fragments: key slot lr of a block lies in half (lr / 8) % 2 at place 4 (2 (lr / 16) + (lr / 4) % 2) + lr % 4
     const bf16x8* const kfrag = pf_lds + ((lr / 8) % 2) * (BP / 2) + hh * 16 + 4 * (2 * (lr / 16) + (lr / 4) % 2) + lr % 4;
@@ -523,8 +543,7 @@ void prefill_attention_lds_kernel(PrefillParams p) {
             for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0[nt][t], pv[t], acc[nt], 0, 0, 0);
     };
 
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    barrier();
+    start();
     int blk = blk_begin;
     for (; blk < blk_first; ++blk) open(blk);      // blocks that only the rows of other waves see
     load_k(blk);
