@@ -45,11 +45,6 @@ __device__ inline size_t v_index(size_t bg, int l_max, int d, int j, int c) {
     return ((bg * (size_t)(l_max / kBlk) + (size_t)(j / kBlk)) * d + c) * kBlk + (j % kBlk);
 }
 
-__device__ inline int clamp_total(int kv_len, int Q, int l_max) {
-    int n = (kv_len < 0 ? 0 : kv_len) + Q;
-    return n > l_max ? l_max : n;
-}
-
 // ---------------------------------------------------------------------------
 // f32 kernel (any even d <= 256): grid (Q, n_q, B), 256 threads.  Keys are taken 256 at a time, from a block boundary:
 // thread t scores key t (its row in 16-byte loads, all in flight), the tile's weights go through LDS, and 256 / d groups
@@ -66,7 +61,7 @@ void attention_f32_kernel(const float* __restrict__ q, const float* __restrict__
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int G = n_q / n_kv, g = h / G;
     const size_t bg = (size_t)b * n_kv + g;
-    int L = kv_len[b]; L = L < 0 ? 0 : L;
+    const int L = cached_rows(kv_len[b], l_max);
     int n_vis = L + i + 1;
     if (n_vis > l_max) n_vis = l_max;
     const int lo = (window > 0 && n_vis > window) ? n_vis - window : 0;      // first row of the sliding window
@@ -192,8 +187,8 @@ void attention_mfma_kernel(AttnParams p) {
     const int lr = lane % 16, lc = lane / 16;
     const int G = p.n_q / p.n_kv, rows = G * p.Q;
     const size_t bg = (size_t)b * p.n_kv + g;
-    int L = p.kv_len[b]; L = L < 0 ? 0 : L;
-    const int n_total = clamp_total(L, p.Q, p.l_max);
+    const int L = cached_rows(p.kv_len[b], p.l_max);
+    const int n_total = L + p.Q < p.l_max ? L + p.Q : p.l_max;
     const int n_blocks = (n_total + kBlk - 1) / kBlk;
     // sliding window: the first query (row L) sees rows from L-W+1 on and later queries start higher, so
     // blocks below that row are skipped altogether; blocks that hold a row below the LAST query's window

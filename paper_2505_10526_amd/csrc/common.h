@@ -26,6 +26,10 @@ static inline int launch_status() {
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Rows cached ahead of a step, as read from device memory: clamped so that a row index formed from it neither leaves the cache
+// unnoticed nor overflows.
+__device__ inline int cached_rows(int kv_len, int l_max) { return kv_len < 0 ? 0 : kv_len > l_max ? l_max : kv_len; }
+
 template <typename T> struct ElemOf;
 template <> struct ElemOf<float> {
     __device__ static inline float load(const float* p) { return *p; }

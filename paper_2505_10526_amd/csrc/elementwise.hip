@@ -144,8 +144,7 @@ __global__ void rope_append_kernel(const T* __restrict__ qkv, const int32_t* __r
         if (live) { x1 *= rstd * ldf(hn + j); x2 *= rstd * ldf(hn + j + half); }
     }
     if (!live) return;
-    int row = kv_len[b];
-    row = (row < 0 ? 0 : row) + i;
+    const int row = cached_rows(kv_len[b], l_max) + i;
     if (head < n_q + n_kv) {
         const double ang = (double)pos[m] * exp2(-2.0 * (double)j / (double)d * log2_theta);
         double sn, cs;
@@ -200,7 +199,7 @@ __global__ void rope_rows_kernel(const T* __restrict__ qkv, const int32_t* __res
     const int half = d / 2;
     const bool live = j < half;
     const int b = m / Lq, i = m % Lq;
-    int L0 = kv_len[b]; L0 = L0 < 0 ? 0 : L0;
+    const int L0 = cached_rows(kv_len[b], l_max);
     int n = n_new[b]; n = n < 0 ? 0 : (n > Lq ? Lq : n);
     if (L0 + n > l_max) n = l_max - L0 > 0 ? l_max - L0 : 0;
     if (i >= n) return;                                  // uniform over the workgroup
@@ -261,7 +260,7 @@ void rope_blocks_kernel(const bf16_t* __restrict__ qkv, const int32_t* __restric
                         int Lq, int n_q, int n_kv, int l_max, int n_blk, int heads_per, double log2_theta) {
     constexpr int HALF = D / 2, TPR = D / 16;            // threads per row, 32 rows
     const int b = blockIdx.x / n_blk, tid = threadIdx.x;
-    int L0 = kv_len[b]; L0 = L0 < 0 ? 0 : L0;
+    const int L0 = cached_rows(kv_len[b], l_max);
     int n = n_new[b]; n = n < 0 ? 0 : (n > Lq ? Lq : n);
     if (L0 + n > l_max) n = l_max - L0 > 0 ? l_max - L0 : 0;
     const int row0 = (L0 / MASSV_V_BLOCK + (int)(blockIdx.x % n_blk)) * MASSV_V_BLOCK;      // first cache row of the block
@@ -393,8 +392,7 @@ __global__ void qkv_finish_kernel(const float* __restrict__ partial, int n_slabs
         if (!live) return;
         x1 *= rstd * (float)hn[j]; x2 *= rstd * (float)hn[j + half];
     }
-    int row = kv_len[b];
-    row = (row < 0 ? 0 : row) + i;
+    const int row = cached_rows(kv_len[b], l_max) + i;
     if (head < n_q + n_kv) {
         const double ang = (double)pos[m] * exp2(-2.0 * (double)j / (double)d * log2_theta);
         double sn, cs;

@@ -582,8 +582,7 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     if (lane >= kF32Rows || m >= M) return;
     if (mats.bias[seg]) { x1 += mats.bias[seg][row0]; x2 += mats.bias[seg][row0 + half]; }
     const int b = m / Q, i = m % Q;
-    int row = kv_len[b];
-    row = (row < 0 ? 0 : row) + i;
+    const int row = cached_rows(kv_len[b], l_max) + i;
     if (seg < 2) {
         const double ang = (double)pos[m] * exp2(-2.0 * (double)j / (double)d * log2_theta);
         double sn, cs;

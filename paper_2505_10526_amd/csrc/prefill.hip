@@ -85,7 +85,7 @@ void prefill_attention_kernel(PrefillParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lr = lane % 32, hh = lane / 32;
     const int G = p.n_q / p.n_kv;
-    int L = p.kv_len[b]; L = L < 0 ? 0 : L;
+    const int L = cached_rows(p.kv_len[b], p.l_max);
     int n = p.n_new[b]; n = n < 0 ? 0 : (n > p.Lq ? p.Lq : n);
     if (L + n > p.l_max) n = p.l_max - L > 0 ? p.l_max - L : 0;
     const int rows = n * G;
@@ -380,7 +380,7 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int lr = lane % 32, hh = lane / 32;
     const int G = p.n_q / p.n_kv;
-    int L = p.kv_len[b]; L = L < 0 ? 0 : L;
+    const int L = cached_rows(p.kv_len[b], p.l_max);
     int n = p.n_new[b]; n = n < 0 ? 0 : (n > p.Lq ? p.Lq : n);
     if (L + n > p.l_max) n = p.l_max - L > 0 ? p.l_max - L : 0;
     const int rows = n * G;
@@ -617,7 +617,7 @@ void prefill_generic_kernel(const float* __restrict__ q, const float* __restrict
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
     const int G = n_q / n_kv, g = h / G;
     const size_t bg = (size_t)b * n_kv + g;
-    int L = kv_len[b]; L = L < 0 ? 0 : L;
+    const int L = cached_rows(kv_len[b], l_max);
     int n = n_new[b]; n = n < 0 ? 0 : (n > Lq ? Lq : n);
     if (L + n > l_max) n = l_max - L > 0 ? l_max - L : 0;
     if (i >= n) return;                                    // uniform over the workgroup

@@ -522,3 +522,33 @@ def test_fp32_logits_rows_and_widths(M, V, H):
         ref = y @ w.double().T
         err = (got.double() - ref).abs().max() / ref.abs().max()
         assert err <= 4 * H ** 0.5 * 2.0 ** -24, (norm is not None, err)
+
+
+@pytest.mark.parametrize("s", [synth.TINY, synth.TINY_BF16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("window", [0, 40])
+def test_lengths_that_cannot_be_leave_the_caches_alone(s, window):
+    """kv_len is read on the device; lengths at and past the end of the cache, up to the largest integer (where adding a
+    row's number overflows), drop every new row: guard rows around the caches keep their bits.  Results are unspecified."""
+    B, Q, l_max, dt = 4, 6, 64, (torch.float32 if s.dtype == "f32" else torch.bfloat16)
+    kv_len = i32([64, 2 ** 31 - 1, 2 ** 31 - 3, 1 << 30])
+    n = B * s.n_kv_heads * l_max * s.head_dim
+
+    def guarded():
+        buf = torch.randn(n + 2 * 65536, device="cuda").to(dt)
+        return buf, buf[65536:65536 + n]
+    (kb, k), (vb, v) = guarded(), guarded()
+    k, v = k.view(B, s.n_kv_heads, l_max, s.head_dim), v.view(B, s.n_kv_heads, l_max // 32, s.head_dim, 32)
+    before = kb.clone(), vb.clone()
+    w = binding.pack_layer_weights({name: None if a is None else to_dev(a, s.dtype) for name, a in synth.layer_weights(s, 3, std=0.05).items()})
+    pos = i32(np.arange(B * Q).reshape(B, Q))
+    cfg = cfg_of(s)
+    cfg.window = window
+    binding.verify_layer(cfg, w, torch.randn(B, Q, s.hidden, device="cuda").to(dt), pos, k, v, kv_len)
+    binding.verify_attention(torch.randn(B, Q, s.n_q_heads, s.head_dim, device="cuda").to(dt), k, v, kv_len, window=window)
+    n_new = i32([Q] * B)
+    qkv = torch.randn(B, Q, (s.n_q_heads + 2 * s.n_kv_heads) * s.head_dim, device="cuda").to(dt)
+    q = binding.rope_append(qkv, pos, kv_len, n_new, k, v, s.n_q_heads, 1e6)
+    o = binding.prefill_attention(torch.randn_like(q), k, v, kv_len, n_new, window=window)
+    torch.cuda.synchronize()
+    assert torch.equal(kb, before[0]) and torch.equal(vb, before[1])
+    assert not q.any() and not o.any()
