@@ -457,11 +457,13 @@ def test_fp32_layer_many_keys_and_unaligned_rows():
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
 
 
-@pytest.mark.parametrize("M,H,V", [(1, 32, 40976), (16, 64, 65600), (17, 96, 45072), (33, 544, 82000), (48, 512, 40960), (64, 160, 20512), (49, 32, 70000)])
+@pytest.mark.parametrize("M,H,V", [(48, 512, 40960), (64, 160, 20512), (16, 64, 65600), (48, 512, 81328), (8, 96, 81328), (32, 64, 81328),
+                                   (33, 544, 82000), (1, 32, 40976), (17, 96, 45072), (48, 96, 122240), (49, 32, 70000), (64, 32, 113888)])
 def test_vocabulary_projection_in_shares(M, H, V):
-    """Vocabularies that take a workgroup two to seven shares of unequal size, at every number of row tiles and down to
-    hidden sizes that leave a wave without a single step: logits against float64 (fp32 sums of H products), and the
-    greedy rule's token, which carries its maximum across shares, against the arg-max of those logits."""
+    """Vocabularies that take a workgroup one (the first), two (the next five), three and up to seven shares (the last), most of
+    unequal size, at every number of row tiles and of tile slots and down to hidden sizes that leave a wave without a
+    single step (plain logits of few rows with empty slots go by a workgroup a share): logits against float64 (fp32 sums of H
+    products), and the greedy rule's token, which carries its maximum across shares, against the arg-max of those logits."""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + V)
     x = torch.randn(M, H, generator=g, device="cuda").to(torch.bfloat16)
