@@ -159,8 +159,13 @@ def _ptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+def _stream_handle():
+    """The current stream as an integer (current_stream().cuda_stream, without the 2.7 us that its Python object takes)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_stream_handle())
 
 
 def dtype_code(t: torch.Tensor) -> int:
@@ -181,10 +186,6 @@ class _Scratch(threading.local):
 
 _scratch = _Scratch()
 _recorded: list = []                # buffers that a recorded graph may use: kept for good
-
-
-def _stream_handle():
-    return torch.cuda.current_stream().cuda_stream
 
 
 def _capturing():

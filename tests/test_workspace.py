@@ -66,6 +66,13 @@ def test_capture_keeps_nothing_and_loses_nothing(host):
 
 
 @pytest.mark.gpu
+def test_stream_handle_is_the_current_streams():
+    assert binding._stream_handle() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(torch.cuda.Stream()) as _:
+        assert binding._stream_handle() == torch.cuda.current_stream().cuda_stream != torch.cuda.default_stream().cuda_stream
+
+
+@pytest.mark.gpu
 def test_two_streams_at_once():
     """Split products on two streams, no workspace given: each result is the one it has alone."""
     g = torch.Generator(device="cuda")
