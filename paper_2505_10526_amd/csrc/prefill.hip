@@ -4,13 +4,14 @@
 // of new positions per sequence instead of gamma+1, so the work is a dense contraction and the matrix cores are
 // the roof, not HBM.
 //
-// bf16 kernel:
+// bf16, two kernels: prefill_attention_kernel (d <= 128) and, for d = 256 and launches that do not fill the chip,
+// prefill_attention_lds_kernel (described where it stands).  The first:
 //   * The caches are read in the library's blocked layouts; a wave's operands of both products are 16-byte loads per
 //     lane straight into registers, no LDS staging and no transposes.
 //   * The G query heads that share a KV head are stacked with the positions into rows (row = position * G + head),
 //     so every key / value tile fetched serves all G heads.
-//   * At d <= 128 a wave owns RT = 2 tiles of 32 stacked rows for the whole key range (d = 256 and small launches: see the kernel
-//     below): Q stays in registers as the B operand of v_mfma_f32_32x32x16_bf16, scores are formed transposed
+//   * A wave owns two tiles of 32 stacked rows for the whole key range: Q stays in registers as the B operand of
+//     v_mfma_f32_32x32x16_bf16, scores are formed transposed
 //     (S^T = K Q^T) so that the probabilities already sit in the operand layout of O^T += V^T P^T, and the streaming
 //     softmax keeps (reference, sum, O) in registers.  Nothing is merged between waves; each writes its own rows.
 //   * The four waves of a workgroup take neighbouring row ranges, so they walk the same key blocks at nearly
@@ -65,7 +66,7 @@ __device__ inline float pf_max3(float a, float b, float c) {
 
 // ---------------------------------------------------------------------------
 // A lone wave per SIMD gets a 32x32x16 matrix instruction out every ~40 cycles (against ~31 for the 16x16x32 form
-// that does half the work).  A wave owns RT tiles of 32 stacked rows.
+// that does half the work).  A wave owns two tiles of 32 stacked rows.
 //   S^T tile (32 key slots x 32 rows): lane l holds row l % 32 and the slots 8 (v / 4) + 4 (l / 32) + v % 4, v = 0..15.
 //   Key slot rho of a block carries key 16 (g / 2) + 8 h + 4 (g % 2) + r (rho = 8 g + 4 h + r), so that the lane's
 //   values v = 8 t .. 8 t + 7 are the keys 16 t + 8 (l / 32) + (0..7): as they stand they are the B operand of step t
@@ -73,9 +74,10 @@ __device__ inline float pf_max3(float a, float b, float c) {
 // ---------------------------------------------------------------------------
 __device__ inline float pf_xor32_max(float v) { return fmaxf(v, __shfl_xor(v, 32, kWave)); }
 
-template <int D, int RT>
+template <int D>
 __global__ __launch_bounds__(kPfThreads)
 void prefill_attention_kernel(PrefillParams p) {
+    constexpr int RT = 2;               // row tiles of a wave
     constexpr int KS = D / 16;          // 16-wide k-steps of the score product
     constexpr int NT = D / 32;          // 32-dim tiles of the output
     constexpr int RW = RT * 32;         // stacked rows per wave
@@ -360,9 +362,10 @@ void prefill_attention_kernel(PrefillParams p) {
 // A value block's pieces (8 keys of a dim) lie in LDS at place c ^ (dim / 4) % 4 of the dim's four: the 32 dims of a
 // fragment are 64 bytes apart, which as they lie in the cache is four lanes to a bank.
 // Waves without rows only bring their share of the blocks in (as long as they multiplied the last row along, calls of up to 32
-// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 4 to 6 % faster: 16 / 8 heads, one row on
-// 100 cached 9.0 -> 10.2 -> 9.3 us).  What it does not win: ungrouped heads under a window, where the four waves'
-// blocks are the union of what each sees (4 / 4 heads, window 512, 80 rows 29.8 -> 30.9).
+// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 2 % slower to 6 % faster: 16 / 8 heads,
+// one row behind 100 cached ones 9.0, 10.2, now 9.3 us, behind 3000 92.5, 99.0, now 85).  What it does not win: ungrouped
+// heads under a window, where the blocks of a workgroup are the union of what its waves see (4 / 4 heads, window 512, 80 rows
+// 29.8, now 30.9).
 // d = 256, 4 x 2000 positions, 16 / 8 heads: 252 -> 172 us (0.52 -> 0.76 PFLOP/s; refilling each operand set early, without LDS:
 // 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
 // ---------------------------------------------------------------------------
@@ -445,8 +448,8 @@ void prefill_attention_lds_kernel(PrefillParams p) {
         if (blk_begin + 1 < blk_end) request(blk_begin + 1);
         if (blk_begin + 2 < blk_end) request(blk_begin + 2);
     };
+    request_first();
     if (r0 >= rows) {                              // a wave past the last row only brings its share of the blocks in
-        request_first();
         start();
         for (int blk = blk_begin; blk < blk_end; ++blk) open(blk);
         return;
@@ -463,7 +466,6 @@ void prefill_attention_lds_kernel(PrefillParams p) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 16 + hh * 8);
     }
-    request_first();
 
     // fragments: key slot lr of a block lies in half (lr / 8) % 2 at place 4 (2 (lr / 16) + (lr / 4) % 2) + lr % 4
     const bf16x8* const kfrag = pf_lds + ((lr / 8) % 2) * (BP / 2) + hh * 16 + 4 * (2 * (lr / 16) + (lr / 4) % 2) + lr % 4;
@@ -666,13 +668,13 @@ void prefill_generic_kernel(const float* __restrict__ q, const float* __restrict
     if (tid < d) out[(((size_t)b * Lq + i) * n_q + h) * d + tid] = acc / l_run;
 }
 
-template <int D, int RT>
+template <int D>
 static int launch_prefill(const massv_attn_desc& a, PrefillParams p, hipStream_t st) {
     const int rows_max = a.n_query * (a.n_q_heads / a.n_kv_heads);
-    const int per_wg = kPfWaves * RT * 32;
+    const int per_wg = kPfWaves * 64;
     p.n_tiles = (rows_max + per_wg - 1) / per_wg;
     if (p.n_tiles > 65535) return MASSV_EUNSUPPORTED;
-    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_kernel<D, RT>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
+    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_kernel<D>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
                   dim3(kPfThreads), 0, st, p);
     return launch_status();
 }
@@ -749,8 +751,8 @@ extern "C" int massv_prefill_attention(const massv_attn_desc* desc, const void* 
     if (a.head_dim == 64) few = few || (!banded && wide <= 256 && a.l_max / 8 <= a.n_query);
     else few = few || (!banded && !n_bidir && wide <= 224 && tiles >= 24 && (int64_t)a.l_max * 4 <= (int64_t)a.n_query * 5 + 128);
     switch (a.head_dim) {
-        case 64: return few ? launch_prefill_lds<64>(a, p, st) : launch_prefill<64, 2>(a, p, st);
-        case 128: return few ? launch_prefill_lds<128>(a, p, st) : launch_prefill<128, 2>(a, p, st);
+        case 64: return few ? launch_prefill_lds<64>(a, p, st) : launch_prefill<64>(a, p, st);
+        case 128: return few ? launch_prefill_lds<128>(a, p, st) : launch_prefill<128>(a, p, st);
         case 256: return launch_prefill_lds<256>(a, p, st);
     }
     return MASSV_EUNSUPPORTED;
