@@ -119,9 +119,6 @@ def test_repeatable_bits_and_pack_roundtrip():
     assert torch.equal(a, b)
 
 
-# ---------------------------------------------------------------------------
-# sliding-window layers of the Gemma 3 targets (Section 5, "Models")
-# ---------------------------------------------------------------------------
 @pytest.mark.parametrize("splits", [7, 8, 9, 16, 17, 33, 64])
 @pytest.mark.parametrize("full", [True, False])
 def test_merge_of_many_splits(splits, full):
@@ -133,6 +130,9 @@ def test_merge_of_many_splits(splits, full):
     assert_close(got, ref, TOL_BF16, f"{splits} splits, full={full}")
 
 
+# ---------------------------------------------------------------------------
+# sliding-window layers of the Gemma 3 targets (Section 5, "Models")
+# ---------------------------------------------------------------------------
 @pytest.mark.parametrize("window", [1, 2, 6, 31, 32, 33, 64, 100, 300, 5000])
 def test_window_bf16_d128_ragged(window):
     """Windows smaller than the query count, at and around block boundaries, larger than the cache;
