@@ -362,10 +362,9 @@ void prefill_attention_kernel(PrefillParams p) {
 // A value block's pieces (8 keys of a dim) lie in LDS at place c ^ (dim / 4) % 4 of the dim's four: the 32 dims of a
 // fragment are 64 bytes apart, which as they lie in the cache is four lanes to a bank.
 // Waves without rows only bring their share of the blocks in (as long as they multiplied the last row along, calls of up to 32
-// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 2 % slower to 6 % faster: 16 / 8 heads,
-// one row behind 100 cached ones 9.0, 10.2, now 9.3 us, behind 3000 92.5, 99.0, now 85).  What it does not win: ungrouped
-// heads under a window, where the blocks of a workgroup are the union of what its waves see (4 / 4 heads, window 512, 80 rows
-// 29.8, now 30.9).
+// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 1 % slower to 8 % faster: 16 / 8 heads,
+// one row behind 100 cached ones 9.2, 10.4, now 9.3 us, behind 3000 92.3, 98.9, now 86.1).  What it does not win: two blocks
+// of ungrouped heads (4 / 4 heads, 40 rows 7.8, now 8.0), where a barrier costs more than the shared blocks save.
 // d = 256, 4 x 2000 positions, 16 / 8 heads: 252 -> 172 us (0.52 -> 0.76 PFLOP/s; refilling each operand set early, without LDS:
 // 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
 // ---------------------------------------------------------------------------
@@ -429,7 +428,9 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     };
     // Opens block blk: block blk + 1 has landed for every wave (a wave's requests complete in order; those of blk + 2 may
     // still be on their way), everybody is done with block blk - 1, and its place takes block blk + 3.
+    // (the last block needs none of it: it landed when the one before was opened, or at the start)
     auto open = [&](int blk) {
+        if (blk + 1 >= blk_end) return;
         if (!DIRECT) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         else if (blk + 2 < blk_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
