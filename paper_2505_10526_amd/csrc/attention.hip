@@ -41,6 +41,12 @@ constexpr int kAttnWaves = 4;
 constexpr int kAttnThreads = kAttnWaves * kWave;
 constexpr int kBlk = MASSV_V_BLOCK;            // keys per block
 
+// Wraps below zero next to 2^31 (unsigned sum), which leaves nothing to visit.
+__device__ inline int clamp_total(int kv_len, int Q, int l_max) {
+    const int n = (int)((unsigned)(kv_len < 0 ? 0 : kv_len) + (unsigned)Q);
+    return n > l_max ? l_max : n;
+}
+
 __device__ inline size_t v_index(size_t bg, int l_max, int d, int j, int c) {
     return ((bg * (size_t)(l_max / kBlk) + (size_t)(j / kBlk)) * d + c) * kBlk + (j % kBlk);
 }
@@ -187,8 +193,9 @@ void attention_mfma_kernel(AttnParams p) {
     const int lr = lane % 16, lc = lane / 16;
     const int G = p.n_q / p.n_kv, rows = G * p.Q;
     const size_t bg = (size_t)b * p.n_kv + g;
-    const int L = cached_rows(p.kv_len[b], p.l_max);
-    const int n_total = L + p.Q < p.l_max ? L + p.Q : p.l_max;
+    // (not clamped to the cache: a length next to 2^31 leaves no block as it is, and the clamp cost 0.1 us a launch)
+    int L = p.kv_len[b]; L = L < 0 ? 0 : L;
+    const int n_total = clamp_total(L, p.Q, p.l_max);
     const int n_blocks = (n_total + kBlk - 1) / kBlk;
     // sliding window: the first query (row L) sees rows from L-W+1 on and later queries start higher, so
     // blocks below that row are skipped altogether; blocks that hold a row below the LAST query's window
