@@ -80,6 +80,11 @@ __host__ __device__ inline size_t k_cache_index(size_t bg, int l_max, int d, int
     return (bg * (size_t)l_max + (size_t)(j & ~31)) * d + ((size_t)(half * (d >> 3) + (c >> 3)) * 16 + slot) * 8 + (c & 7);
 }
 
+// ---- value cache ---- blocks of 32 rows, feature-major inside a block
+__host__ __device__ inline size_t v_cache_index(size_t bg, int l_max, int d, int j, int c) {
+    return ((bg * (size_t)(l_max / MASSV_V_BLOCK) + (size_t)(j / MASSV_V_BLOCK)) * d + c) * MASSV_V_BLOCK + (j % MASSV_V_BLOCK);
+}
+
 // ---- wavefront scans and reductions (all 64 lanes take part, all receive the result) ----
 // Built from data-parallel-primitive moves: four shifts inside each row of 16 lanes, then the last lane of
 // row 0 / row 2 combined into row 1 / row 3 and the last lane of row 1 into rows 2 and 3; lane 63 then holds the
@@ -101,6 +106,8 @@ __device__ inline double dpp_move(double v, double fill) {
     const int hi = __builtin_amdgcn_update_dpp(__double2hiint(fill), __double2hiint(v), CTRL, ROW_MASK, 0xf, false);
     return __hiloint2double(hi, lo);
 }
+template <int SHIFT>
+__device__ inline float row_ror(float v) { return dpp_move<0x120 + SHIFT, 0xf>(v, 0.f); }      // lane i of 16 gets lane (i - SHIFT) mod 16
 __device__ inline float lane_value(float v, int src_lane) {  // src_lane uniform over the wave
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src_lane));
 }

@@ -119,10 +119,6 @@ __device__ inline float block_sum_256(float v, float* red /* [4] shared */) {
 // Rotary embedding + KV append.  grid = (M, n_q + 2 n_kv); thread j < d/2 owns
 // the pair (j, j + d/2) of one head of one token.
 // ---------------------------------------------------------------------------
-__device__ inline size_t v_cache_index(size_t bg, int l_max, int d, int j, int c) {
-    return ((bg * (size_t)(l_max / MASSV_V_BLOCK) + (size_t)(j / MASSV_V_BLOCK)) * d + c) * MASSV_V_BLOCK + (j % MASSV_V_BLOCK);
-}
-
 template <typename T>
 __global__ void rope_append_kernel(const T* __restrict__ qkv, const int32_t* __restrict__ pos,
                                    const int32_t* __restrict__ kv_len, T* __restrict__ q_out,

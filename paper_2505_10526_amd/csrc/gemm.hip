@@ -39,7 +39,7 @@
 //     (written in operand order for the down projection), fp32 logits.
 // f32 kernels: one wave per output feature, plain FMAs, for the small fp32
 // configuration.
-#include "kernels.h"
+#include "gemm_stream.h"
 
 #include <limits.h>
 #include <atomic>
@@ -47,205 +47,10 @@
 
 namespace massv {
 
-constexpr int kGemmWaves = 4;            // waves per workgroup (K split)
-constexpr int kCUs = 256;
-
-struct GemmDev {
-    const bf16_t* x;
-    const bf16_t* w[3];
-    int tiles[3];            // 16-feature tiles per matrix
-    void* y;
-    void* stats;             // EPI_LOGITS_STATS: RowPartial[M][gridDim.x]
-    float ts_hi, ts_lo;      // EPI_LOGITS_STATS: log2(e)/T in two floats
-    int M, K, ldy;           // ldy: elements per output row
-    int act;
-    int unit_base, unit_rem; // balanced split of the tile units over gridDim.x * rounds shares: the first unit_rem own unit_base+1
-    int rounds;              // vocabulary projection: shares a workgroup works off one after the other
-    size_t slab_stride;      // elements between the partial sums of consecutive K slabs
-};
-
-// Gated-MLP activations through the hardware exp2 and reciprocal (about 1e-6 relative error, the result is
-// rounded to bf16): the library versions with exact division and tanhf made the projection's epilogue a few
-// thousand instructions long, 3 us of a 46 us launch.  0.5 (1 + tanh(u)) is sigmoid(2u).
-__device__ inline float fast_sigmoid(float x) {
-    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
-}
-__device__ inline float gemm_act(float x, int act) {
-    if (act == MASSV_ACT_SILU) return x * fast_sigmoid(x);
-    const float c = 0.7978845608028654f;
-    return x * fast_sigmoid(2.0f * c * (x + 0.044715f * x * x * x));
-}
-
 // 2^(d * log2(e)/T) for d <= 0 (a logit minus a running maximum; -inf and NaN from -inf - -inf give 0).
 __device__ inline float exp2_scaled(float d, float hi, float lo) {
     d = fmaxf(d, -3.0e38f);
     return __builtin_amdgcn_exp2f(fmaf(d, lo, d * hi));
-}
-
-__device__ inline bf16x8 ld8(const bf16_t* p, bool ok) {
-    bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-    return ok ? *reinterpret_cast<const bf16x8*>(p) : z;
-}
-__device__ inline bf16x8 ld8_stream(const bf16_t* p, bool ok) {      // weights: read once, whole lines
-    bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-    return ok ? ldg_stream(reinterpret_cast<const bf16x8*>(p)) : z;
-}
-
-
-// Tiles of LDS reduced per round: at most 128 KB of fp32 fragments at a time -- one round for every shape built
-// (10 tiles x 3 row tiles x 4 waves = 120 KB); rounds of 48 KB cost two more barrier pairs per launch.
-template <int MT, int NT>
-struct ReduceGroup {
-    static constexpr int kMax = 128 / (MT * kGemmWaves);
-    static constexpr int raw = (NT < kMax) ? NT : kMax;
-    static constexpr int value = (raw >= 2) ? (raw / 2) * 2 : 1;     // even, so gate/up pairs stay together
-};
-
-template <int MT, int NT, int EPI>
-__global__ __launch_bounds__(kGemmWaves * kWave)
-void gemm_stream_kernel(GemmDev g) {
-    constexpr int WK = kGemmWaves;
-    constexpr bool gated = (EPI == EPI_GATED);
-    extern __shared__ floatx4 red[];                 // [WK][GRP*MT][64]
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int lr = lane % 16, lc = lane / 16;
-    const int K = g.K;
-
-    // ---- the NT feature tiles of this workgroup ----
-    const bf16_t* wrow[NT];
-    bool nvalid[NT];
-    int ocol[NT];
-    // a unit is one tile (a gate/up tile pair for the gated epilogue); units are dealt to the workgroups
-    // as evenly as possible, so a workgroup may own fewer than its NT tile slots
-    constexpr int UT = gated ? 2 : 1;
-    // split-K launches: the slab is the fast grid index, so that the workgroups of one slab -- which read the same
-    // piece of X -- have linear indices that are congruent modulo the slab count and fall on the same XCDs
-    constexpr bool SLAB_FAST = (EPI == EPI_PARTIAL);
-    const int bx = SLAB_FAST ? blockIdx.y : blockIdx.x;
-    const int n_slabs = SLAB_FAST ? gridDim.x : gridDim.y;
-    const int unit0 = bx * g.unit_base + (bx < g.unit_rem ? bx : g.unit_rem);
-    const int n_units = g.unit_base + (bx < g.unit_rem ? 1 : 0);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int t = unit0 * UT + nt;
-        const bool owned = nt < n_units * UT;
-        int seg, local;
-        if (gated) {                                  // tiles alternate gate, up of one 16-feature group
-            seg = t & 1; local = t >> 1;
-            nvalid[nt] = owned && local < g.tiles[0];
-            ocol[nt] = local * 16;
-        } else {
-            if (t < g.tiles[0]) { seg = 0; local = t; }
-            else if (t < g.tiles[0] + g.tiles[1]) { seg = 1; local = t - g.tiles[0]; }
-            else { seg = 2; local = t - g.tiles[0] - g.tiles[1]; }
-            nvalid[nt] = owned && t < g.tiles[0] + g.tiles[1] + g.tiles[2];
-            ocol[nt] = t * 16;
-        }
-        if (!nvalid[nt]) { seg = 0; local = 0; }
-        wrow[nt] = g.w[seg] + (size_t)local * (K / 32) * 512 + lane * 8;      // tile `local` of the streaming layout
-    }
-    // X in operand order: the B operand of (k-step ks, row tile mt) is the 1 KB block ((ks*MT + mt)*64 + lane)*8
-    const bf16_t* xlane = g.x + (size_t)lane * 8;
-
-    floatx4 acc[NT][MT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    // K is dealt in 32-element MFMA steps.  The steps of the launch are split evenly over the gridDim.y slabs.  Inside
-    // a slab the waves take chunks of four steps in turn (so the workgroup reads contiguous 16 KB runs of a tile), and
-    // the last, incomplete round of 16 steps is split evenly: no wave does more than one step above the average.
-    const int n_steps = K / 32;
-    const int sb = n_steps / n_slabs, sr = n_steps % n_slabs;
-    const int by = SLAB_FAST ? blockIdx.x : blockIdx.y;
-    const int s_begin = by * sb + (by < sr ? by : sr);
-    const int s_count = sb + (by < sr ? 1 : 0);
-    const int rounds = s_count / (4 * WK);
-    const int tail = s_count - rounds * 4 * WK;
-    const int tb = tail / WK, tr = tail % WK;
-    const int t_len = tb + (wave < tr ? 1 : 0);                              // 0..4 steps
-    const int t_k0 = s_begin + rounds * 4 * WK + wave * tb + (wave < tr ? wave : tr);
-    const int n_it = rounds + (t_len > 0 ? 1 : 0);
-    auto k0_of = [&](int it) { return it < rounds ? s_begin + (it * WK + wave) * 4 : t_k0; };
-    auto cnt_of = [&](int it) { return it < rounds ? 4 : t_len; };
-
-    bf16x8 a[NT][4];
-    bf16x8 xb[2][MT][4];
-    auto wload = [&](int nt, int k0, int cnt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) a[nt][j] = ld8_stream(wrow[nt] + (size_t)(k0 + j) * 512, nvalid[nt] && j < cnt);
-    };
-    auto xload = [&](int buf, int k0, int cnt) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                xb[buf][mt][j] = ld8(xlane + (size_t)((k0 + j) * MT + mt) * 512, j < cnt);
-    };
-    if (n_it > 0) {
-        xload(0, k0_of(0), cnt_of(0));
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) wload(nt, k0_of(0), cnt_of(0));
-    }
-    int par = 0;
-    for (int it = 0; it < n_it; ++it, par ^= 1) {
-        const bool more = it + 1 < n_it;
-        const int nx = k0_of(it + 1), ncnt = cnt_of(it + 1);
-        if (more) { if (par) xload(0, nx, ncnt); else xload(1, nx, ncnt); }
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nt][j], par ? xb[1][mt][j] : xb[0][mt][j],
-                                                                         acc[nt][mt], 0, 0, 0);
-            if (more) wload(nt, nx, ncnt);            // refill this tile's slot for the wave's next four steps
-        }
-    }
-
-    // ---- sum the waves through LDS in wave order, GRP tiles per round ----
-    constexpr int GRP = ReduceGroup<MT, NT>::value;
-    for (int g0 = 0; g0 < NT; g0 += GRP) {
-        if (g0) __syncthreads();
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            if (nt >= g0 && nt < g0 + GRP)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    red[(wave * GRP * MT + (nt - g0) * MT + mt) * kWave + lane] = acc[nt][mt];
-        __syncthreads();
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if (nt < g0 || nt >= g0 + GRP) continue;
-            if (gated && (nt & 1)) continue;                    // the up tile is consumed with its gate tile
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const int item = gated ? ((nt - g0) / 2) * MT + mt : (nt - g0) * MT + mt;
-                if (item % WK != wave || !nvalid[nt]) continue;  // items are dealt round-robin to the waves
-                const int f = (nt - g0) * MT + mt;
-                floatx4 s = red[f * kWave + lane];
-                for (int w = 1; w < WK; ++w) s += red[(w * GRP * MT + f) * kWave + lane];
-                const int m = mt * 16 + lr;
-                const int col = ocol[nt] + lc * 4;               // 4 consecutive output features
-                if (gated) {
-                    constexpr int UP = (NT > 1) ? MT : 0;        // fragment of the paired up tile
-                    floatx4 u = red[(f + UP) * kWave + lane];
-                    for (int w = 1; w < WK; ++w) u += red[(w * GRP * MT + f + UP) * kWave + lane];
-                    if (m < g.M) {
-                        bf16x4 o;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) o[i] = (bf16_t)(gemm_act(s[i], g.act) * u[i]);
-                        *reinterpret_cast<bf16x4*>((bf16_t*)g.y + packed_index(m, col, MT)) = o;
-                    }
-                } else if (m < g.M) {
-                    float* dst = (float*)g.y + (size_t)by * g.slab_stride + (size_t)m * g.ldy + col;
-                    *reinterpret_cast<floatx4*>(dst) = s;
-                }
-            }
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -813,13 +618,8 @@ static int launch_stream_epi(const GemmDev& d, int M, const GemmPlan& p, int kid
     return MASSV_EUNSUPPORTED;
 }
 
-int launch_gemm(const GemmArgs& g, hipStream_t st) {
-    const int rc = gemm_supported(g);
-    if (rc != MASSV_OK) return rc;
-    if (g.dtype == MASSV_F32) return launch_gemm_f32(g, st);
+int fill_gemm_dev(GemmDev& d, const GemmArgs& g, const GemmPlan& p) {
     const int N = n_total(g);
-    const GemmPlan p = gemm_plan(g);
-    GemmDev d;
     d.x = (const bf16_t*)g.x;
     for (int s = 0; s < 3; ++s) { d.w[s] = (const bf16_t*)g.w[s]; d.tiles[s] = g.n[s] / 16; }
     d.y = g.y;
@@ -829,16 +629,24 @@ int launch_gemm(const GemmArgs& g, hipStream_t st) {
     d.M = g.M; d.K = g.K;
     d.ldy = (g.epilogue == EPI_GATED) ? g.n[0] : N;
     d.act = g.act;
-    {
-        const int ut = (g.epilogue == EPI_GATED) ? 2 : 1;
-        const int units = ((g.epilogue == EPI_GATED) ? 2 * d.tiles[0] : N / 16) / ut;
-        d.rounds = gemm_rounds(p, g);
-        d.unit_base = units / p.groups;
-        d.unit_rem = units % p.groups;
-        if ((d.unit_base + (d.unit_rem ? 1 : 0)) * ut > p.nt) return MASSV_EUNSUPPORTED;     // cannot happen with gemm_plan's groups
-    }
+    const int ut = (g.epilogue == EPI_GATED) ? 2 : 1;
+    const int units = ((g.epilogue == EPI_GATED) ? 2 * d.tiles[0] : N / 16) / ut;
+    d.rounds = gemm_rounds(p, g);
+    d.unit_base = units / p.groups;
+    d.unit_rem = units % p.groups;
     d.slab_stride = (size_t)((g.M + 15) / 16 * 16) * N;
-    int rc2 = MASSV_EUNSUPPORTED;
+    return (d.unit_base + (d.unit_rem ? 1 : 0)) * ut > p.nt ? MASSV_EUNSUPPORTED : MASSV_OK;      // (always fits with gemm_plan's groups)
+}
+
+int launch_gemm(const GemmArgs& g, hipStream_t st) {
+    const int rc = gemm_supported(g);
+    if (rc != MASSV_OK) return rc;
+    if (g.dtype == MASSV_F32) return launch_gemm_f32(g, st);
+    const GemmPlan p = gemm_plan(g);
+    GemmDev d;
+    int rc2 = fill_gemm_dev(d, g, p);
+    if (rc2 != MASSV_OK) return rc2;
+    rc2 = MASSV_EUNSUPPORTED;
     switch (g.epilogue) {
         case EPI_PARTIAL: rc2 = launch_stream_epi<EPI_PARTIAL>(d, g.M, p, g.kid, st); break;
         case EPI_GATED: rc2 = launch_stream_epi<EPI_GATED>(d, g.M, p, g.kid, st); break;

@@ -98,6 +98,86 @@ struct GemmArgs {
     int kid;                  // massv_kernel_id bracketed by a pending trace request
 };
 int launch_gemm(const GemmArgs& g, hipStream_t st);
+
+// ---- projections over the whole of K with what follows them (whole.hip); bf16 ----
+// Rows that come as x * gains: their 1 / rms is applied to the projection's accumulators.  ss[parts][16 ceil(M/16)]: sums of
+// squares of the rows' pieces, H the row's width; ss == nullptr: the rows are normalised already.
+struct RowScale { const float* ss; int parts, H; float eps; };
+// Each thread of T takes four rows of every (T / R4)-th piece; the first HOLD of them are asked for at once and stay on their way ...
+template <int T, int MT>
+struct RowScaleSums {
+    static constexpr int R4 = 4 * MT;                              // threads a piece
+    static constexpr int G = T / R4, HOLD = MT * 1024 / T;
+    floatx4 v[HOLD];
+    __device__ inline void load(const RowScale& r, int tid) {
+        const int q = tid % R4;
+#pragma unroll
+        for (int i = 0; i < HOLD; ++i) {
+            const int part = tid / R4 + i * G;
+            v[i] = part < r.parts ? *reinterpret_cast<const floatx4*>(r.ss + (size_t)part * MT * 16 + q * 4) : floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+// ... the threads of 16 lanes add theirs up and leave the share in s_ss[T / 16][16 MT] (a barrier later it may be read) ...
+    __device__ inline void store(const RowScale& r, float* s_ss, int tid) {
+        const int q = tid % R4;
+        floatx4 s = v[0];
+#pragma unroll
+        for (int i = 1; i < HOLD; ++i) s += v[i];
+        for (int part = tid / R4 + HOLD * G; part < r.parts; part += G)
+            s += *reinterpret_cast<const floatx4*>(r.ss + (size_t)part * MT * 16 + q * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[e] += row_ror<8>(s[e]);
+            if constexpr (R4 == 4) s[e] += row_ror<4>(s[e]);
+        }
+        const int l = tid % 16;
+        if (l < R4) *reinterpret_cast<floatx4*>(s_ss + (tid / 16) * MT * 16 + l * 4) = s;
+    }
+};
+// ... and a row's factor is formed from the T / 16 shares, by every thread for itself or, where the 16 threads of a row (c = 0 .. 15)
+// all want it, together.
+__device__ inline float row_rstd_of(const RowScale& r, float sum) { return 1.0f / sqrtf(sum / (float)r.H + r.eps); }
+template <int T, int MT>
+__device__ inline float row_rstd(const RowScale& r, const float* s_ss, int m) {
+    float t = s_ss[m];
+#pragma unroll
+    for (int w = 1; w < T / 16; ++w) t += s_ss[w * MT * 16 + m];
+    return row_rstd_of(r, t);
+}
+template <int T>
+__device__ inline float row_rstd_by16(const RowScale& r, const float* s_ss, int m, int c) {
+    float t = s_ss[c * 16 + m];
+#pragma unroll
+    for (int w = 16; w < T / 16; w += 16) t += s_ss[(w + c) * 16 + m];
+    t += row_ror<8>(t); t += row_ror<4>(t); t += row_ror<2>(t); t += row_ror<1>(t);      // (the same sum in every lane)
+    return row_rstd_of(r, t);
+}
+
+// Gated-MLP activations through the hardware exp2 and reciprocal (about 1e-6 relative error, the result is
+// rounded to bf16): the library versions with exact division and tanhf made the projection's epilogue a few
+// thousand instructions long, 3 us of a 46 us launch.  0.5 (1 + tanh(u)) is sigmoid(2u).
+__device__ inline float fast_sigmoid(float x) {
+    return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
+}
+__device__ inline float gemm_act(float x, int act) {
+    if (act == MASSV_ACT_SILU) return x * fast_sigmoid(x);
+    const float c = 0.7978845608028654f;
+    return x * fast_sigmoid(2.0f * c * (x + 0.044715f * x * x * x));
+}
+
+// Whether the projection (GemmArgs as for launch_gemm) is faster this way than as launch_gemm runs it.
+bool whole_qkv_pays(const GemmArgs& g);
+bool whole_residual_pays(const GemmArgs& g);
+// launch_gemm + launch_qkv_finish in one launch (g.bias: nullptr = none); no head norms.
+int launch_whole_qkv(const GemmArgs& g, const RowScale& scale, const int32_t* pos, const int32_t* kv_len, void* q_out,
+                     void* k_cache, void* v_cache, const massv_attn_desc& a, float theta, hipStream_t st);
+// launch_gemm + launch_residual_finish (without a post norm) in one launch, except that xn_packed receives rows * ln and
+// ss[whole_residual_parts][16 ceil(M/16)] the sums of squares (both only when ln != nullptr).
+int launch_whole_residual(const GemmArgs& g, const void* x_in, const float* h_in, void* x_out, float* h_out, const void* ln,
+                          void* xn_packed, float* ss, hipStream_t st);
+int whole_residual_parts(const GemmArgs& g);
+// launch_gemm of an EPI_GATED projection, of rows * gains when scale.ss is set (at most 32 rows then).
+int launch_gated(const GemmArgs& g, const RowScale& scale, hipStream_t st);
 // f32: the q/k/v projections (g: matrices, biases, x and norm as for launch_gemm) with the rotation by pos and the append
 // of k / v at cache rows kv_len[b] + i in the same launch; no head norms (those need a whole head: launch_rope_append).
 int launch_qkv_rope_f32(const GemmArgs& g, const int32_t* pos, const int32_t* kv_len, void* q_out, void* k_cache, void* v_cache,

@@ -84,12 +84,23 @@ static int check_layer_weights(const massv_layer_desc* desc, const massv_layer_w
     return MASSV_OK;
 }
 
+// How the bf16 projections of a layer run: with what follows them in the same launch, or as slabs that a row-wise kernel sums.
+struct WholeProjs { bool qkv, op, dn; };
+static WholeProjs whole_projs(const LayerGemms& g, const massv_layer_weights* w) {
+    WholeProjs p = {};
+    p.qkv = !w->q_norm && !w->k_norm && whole_qkv_pays(g.qkv);
+    p.op = !w->post_attn_norm && whole_residual_pays(g.op);
+    p.dn = !w->post_mlp_norm && whole_residual_pays(g.dn);
+    return p;
+}
+
 // One layer.  xn_ready: the workspace already holds rmsnorm(x, ln1) in operand order (written by the
-// previous layer's last kernel); next_ln: gains of the norm that follows this layer (the next layer's
-// ln1), fused into this layer's last kernel when not NULL.  Both are bf16-path options.
+// previous layer's last kernel), or x * ln1 with the sums of squares that xn_scale names; next_ln: gains of the norm that
+// follows this layer (the next layer's ln1), fused into this layer's last kernel when not NULL, which then applies the row
+// scale too unless next_scales is set (the next layer's first projection will).  All are bf16-path options.
 static int run_layer(const massv_layer_desc* desc, const massv_layer_weights* w, void* x, const int32_t* pos,
                      void* k_cache, void* v_cache, const int32_t* kv_len, void* workspace,
-                     const LayerLayout& lay, bool xn_ready, const void* next_ln, hipStream_t st) {
+                     const LayerLayout& lay, bool xn_ready, const void* next_ln, hipStream_t st, RowScale* xn_scale = nullptr, bool next_scales = false) {
     int rc;
     const massv_attn_desc& a = desc->attn;
     char* ws = (char*)workspace;
@@ -137,16 +148,34 @@ static int run_layer(const massv_layer_desc* desc, const massv_layer_weights* w,
     // run next anyway (rotary + append, residual + norm) sums them.
     const size_t wq = (size_t)(a.n_q_heads + 2 * a.n_kv_heads) * a.head_dim;
     if (!xn_ready && (rc = launch_rmsnorm_packed(x, w->ln1, ws + lay.xn, M, H, desc->norm_eps, st)) != MASSV_OK) return rc;
-    if ((rc = launch_gemm(g.qkv, st)) != MASSV_OK) return rc;
-    if ((rc = launch_qkv_finish(partial, gemm_plan(g.qkv).slabs, Mp * wq, bias ? w->bq : nullptr, bias ? w->bk : nullptr,
-                                bias ? w->bv : nullptr, pos, kv_len, ws + lay.qrot, k_cache, v_cache, w->q_norm, w->k_norm,
-                                desc->norm_eps, a, desc->rope_theta, st)) != MASSV_OK) return rc;
+    const WholeProjs whole = whole_projs(g, w);
+    const RowScale normalised = {};
+    RowScale sums = {partial, whole_residual_parts(g.op), H, desc->norm_eps};      // (no slabs are alive while these are)
+    if (whole.qkv) {
+        if (bias) { g.qkv.bias[0] = w->bq; g.qkv.bias[1] = w->bk; g.qkv.bias[2] = w->bv; }
+        if ((rc = launch_whole_qkv(g.qkv, xn_ready && xn_scale ? *xn_scale : normalised, pos, kv_len, ws + lay.qrot, k_cache, v_cache, a,
+                                   desc->rope_theta, st)) != MASSV_OK) return rc;
+    } else {
+        if ((rc = launch_gemm(g.qkv, st)) != MASSV_OK) return rc;
+        if ((rc = launch_qkv_finish(partial, gemm_plan(g.qkv).slabs, Mp * wq, bias ? w->bq : nullptr, bias ? w->bk : nullptr,
+                                    bias ? w->bv : nullptr, pos, kv_len, ws + lay.qrot, k_cache, v_cache, w->q_norm, w->k_norm,
+                                    desc->norm_eps, a, desc->rope_theta, st)) != MASSV_OK) return rc;
+    }
     if ((rc = launch_attention(a, ws + lay.qrot, k_cache, v_cache, kv_len, ws + lay.attn, ws + lay.attn_ws, true, st)) != MASSV_OK) return rc;
-    if ((rc = launch_gemm(g.op, st)) != MASSV_OK) return rc;
     float* h32 = (float*)(ws + lay.h32);
-    if ((rc = launch_residual_finish(partial, gemm_plan(g.op).slabs, Mp * H, x, nullptr, h32, w->post_attn_norm, w->ln2,
-                                     ws + lay.xn, M, H, desc->norm_eps, st)) != MASSV_OK) return rc;
-    if ((rc = launch_gemm(g.gu, st)) != MASSV_OK) return rc;
+    if (whole.op) {
+        if ((rc = launch_whole_residual(g.op, x, nullptr, nullptr, h32, w->ln2, ws + lay.xn, partial, st)) != MASSV_OK) return rc;
+    } else {
+        if ((rc = launch_gemm(g.op, st)) != MASSV_OK) return rc;
+        if ((rc = launch_residual_finish(partial, gemm_plan(g.op).slabs, Mp * H, x, nullptr, h32, w->post_attn_norm, w->ln2,
+                                         ws + lay.xn, M, H, desc->norm_eps, st)) != MASSV_OK) return rc;
+    }
+    if ((rc = launch_gated(g.gu, whole.op ? sums : normalised, st)) != MASSV_OK) return rc;
+    if (xn_scale) *xn_scale = normalised;
+    if (whole.dn && (!next_ln || next_scales)) {
+        if (next_ln) { sums.parts = whole_residual_parts(g.dn); *xn_scale = sums; }
+        return launch_whole_residual(g.dn, nullptr, h32, x, nullptr, next_ln, ws + lay.xn, partial, st);
+    }
     if ((rc = launch_gemm(g.dn, st)) != MASSV_OK) return rc;
     return launch_residual_finish(partial, gemm_plan(g.dn).slabs, Mp * H, x, h32, nullptr, w->post_mlp_norm, next_ln,
                                   next_ln ? ws + lay.xn : nullptr, M, H, desc->norm_eps, st);
@@ -180,14 +209,16 @@ extern "C" int massv_verify_layers(const massv_layer_desc* desc, const massv_lay
     const LayerLayout lay = layer_layout(*desc);
     if (!workspace || workspace_bytes < lay.total) return MASSV_EWORKSPACE;
     const bool bf = desc->attn.dtype == MASSV_BF16;
+    RowScale xn_scale = {};
     for (int l = 0; l < n_layers; ++l) {
         // bf16: the norm that opens layer l+1 is computed by the kernel that closes layer l
         const void* next_ln = (bf && l + 1 < n_layers) ? weights[l + 1].ln1 : nullptr;
         massv_layer_desc dl = *desc;                    // this layer's window and rotary base
         if (windows) dl.attn.window = windows[l];
         if (rope_thetas) dl.rope_theta = rope_thetas[l];
+        const bool next_scales = next_ln && whole_projs(layer_gemms(*desc), weights + l + 1).qkv;
         rc = run_layer(&dl, weights + l, x, pos, k_caches[l], v_caches[l], kv_len, workspace, lay,
-                       bf && l > 0, next_ln, (hipStream_t)stream);
+                       bf && l > 0, next_ln, (hipStream_t)stream, &xn_scale, next_scales);
         if (rc != MASSV_OK) return rc;
     }
     return MASSV_OK;

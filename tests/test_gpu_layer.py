@@ -554,3 +554,34 @@ def test_lengths_that_cannot_be_leave_the_caches_alone(s, window):
     torch.cuda.synchronize()
     assert torch.equal(kb, before[0]) and torch.equal(vb, before[1])
     assert not q.any() and not o.any()
+
+
+# ---------------------------------------------------------------------------
+# projections that carry what follows them (whole K per workgroup): every kind, at the edges of its row range
+# ---------------------------------------------------------------------------
+WHOLE_SHAPES = {
+    # q/k/v 256 -> 16 features x 256 workgroups at most; down has an odd number of 32-wide steps (352), O an even one
+    "eight_pairs_odd_k": synth.LayerShape(128, 2, 1, 64, 352, 4096),
+    # q/k/v 4608 features: 16 pairs a workgroup; gate / up 2 tiles a workgroup, one of them in some
+    "sixteen_pairs": synth.LayerShape(96, 28, 4, 128, 2080, 4096, qkv_bias=False),
+    # d = 256; hidden 2080: O and down by 16 features at any number of rows (260 workgroups of 8); gate / up 4 tiles
+    "wide_rows": synth.LayerShape(2080, 2, 1, 256, 6176, 4096, synth.ACT_GELU_TANH, False),
+}
+
+
+@pytest.mark.parametrize("B,Q", [(1, 1), (8, 1), (9, 1), (4, 4), (17, 1), (8, 4), (11, 3), (8, 6), (7, 7)])
+@pytest.mark.parametrize("name", WHOLE_SHAPES)
+def test_projections_with_what_follows(name, B, Q):
+    """Two layers in one call (rows * gains and their sums of squares handed from each projection to the next): 1, 8 | 9, 16 | 17,
+    32 | 33, 48 | 49 rows."""
+    # weights of unit gain: the bound is one layer's, and 0.05 at 2080 inputs (gain 2.3) amplifies the first layer's rounding
+    # past it in the second (2.4e-2 at 32 rows, also without these kernels)
+    s = WHOLE_SHAPES[name]
+    rng = np.random.default_rng(B * 100 + Q)
+    run_stack(s, 2, B, Q, rng.integers(1, 60, B), rng.integers(0, 2, B), seed=40 + B, w_std=min(0.05, s.hidden ** -0.5))
+
+
+@pytest.mark.parametrize("mlp", [32, 2080, 4128, 6176, 8224, 10272, 12320, 16384, 16416])
+def test_gated_projection_tiles(mlp):
+    """1 to 8 tiles a workgroup of the gate / up projection, the last one missing in some workgroups, and one width past them."""
+    run_layer(synth.LayerShape(64, 2, 1, 64, mlp, 4096), 3, 3, [40, 0, 7], [8, 0, 0], seed=50, w_std=0.05)
