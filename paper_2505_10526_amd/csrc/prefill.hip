@@ -4,8 +4,8 @@
 // of new positions per sequence instead of gamma+1, so the work is a dense contraction and the matrix cores are
 // the roof, not HBM.
 //
-// bf16, two kernels: prefill_attention_kernel (d <= 128) and, for d = 256 and launches that do not fill the chip,
-// prefill_attention_lds_kernel (described where it stands).  The first:
+// bf16, three kernels: prefill_attention_kernel (d <= 128), prefill_attention_lds_kernel (d <= 128, launches that do not fill the
+// chip) and prefill_attention_rows16_kernel (d = 256), the latter two described where they stand.  The first:
 //   * The caches are read in the library's blocked layouts; a wave's operands of both products are 16-byte loads per
 //     lane straight into registers, no LDS staging and no transposes.
 //   * The G query heads that share a KV head are stacked with the positions into rows (row = position * G + head),
@@ -353,23 +353,17 @@ void prefill_attention_kernel(PrefillParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// One tile of 32 rows per wave, blocks staged in LDS: for d = 256, and for launches too small to fill the chip (see the
-// dispatch below).  At d = 256 a wave's accumulators, Q and one block of operands fill its registers with one tile, and
-// four waves loading every block for themselves (32 KB each, more than the vector cache holds) were bound by what the
-// die's L2 delivers to a compute unit.  Here the blocks travel into LDS once per workgroup (global_load_lds, a ring of
+// One tile of 32 rows per wave, blocks staged in LDS: for launches of d <= 128 that are too small to fill the chip (see the
+// dispatch below).  The blocks travel into LDS once per workgroup (global_load_lds, a ring of
 // four, two to three blocks ahead, one barrier per block) and the waves take their fragments from there; the
 // exponentials of block i sit between the matrix instructions of block i + 1's scores, which are formed in two chains.
 // A value block's pieces (8 keys of a dim) lie in LDS at place c ^ (dim / 4) % 4 of the dim's four: the 32 dims of a
 // fragment are 64 bytes apart, which as they lie in the cache is four lanes to a bank.
-// Waves without rows only bring their share of the blocks in (as long as they multiplied the last row along, calls of up to 32
-// rows were 4 to 12 % slower than by the kernel that loaded every block for itself; now 1 % slower to 8 % faster: 16 / 8 heads,
-// one row behind 100 cached ones 9.2, 10.4, now 9.3 us, behind 3000 92.3, 98.9, now 86.1).  What it does not win: two blocks
-// of ungrouped heads (4 / 4 heads, 40 rows 7.8, now 8.0), where a barrier costs more than the shared blocks save.
-// d = 256, 4 x 2000 positions, 16 / 8 heads: 252 -> 172 us (0.52 -> 0.76 PFLOP/s; refilling each operand set early, without LDS:
-// 206); second pieces of 4 prompts, 1500 positions on 600 cached, window 1024, image block: 200 -> 152 us.
+// Waves without rows only bring their share of the blocks in (multiplying the last row along made calls of up to 32
+// rows 4 to 12 % slower).
 // ---------------------------------------------------------------------------
 constexpr int kPfRing = 4;
-constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 128 KB at d = 256
+constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 64 KB at d = 128
 
 template <int D, bool DIRECT>
 __global__ __launch_bounds__(kPfThreads)
@@ -609,6 +603,204 @@ void prefill_attention_lds_kernel(PrefillParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// d = 256: 16 rows per wave, eight waves, two a SIMD.  With 32 rows a wave is alone on its SIMD (accumulators and Q take 192
+// registers) and its scores, softmax and second product follow one another; with 16 one wave's softmax, which goes first
+// (s_setprio), runs beside the other's matrix instructions.  Twice the LDS reads for it: 37 % of the cycles instead of 17, at 256 bytes a
+// cycle; matrix cores 34 -> 38 % busy at 2048 positions behind 6000 (the rest: both waves wait for the same fragments behind a
+// barrier).  Blocks come in pairs through a ring of two pairs, one barrier a pair; half of a block's keys are read ahead, behind the
+// second product of the block before.
+// Key fragments lie as in the cache, 1 KB each.  Piece c (8 keys) of dim v lies at place c ^ (-(v / 4)) % 4 of the dim's four:
+// a fragment's 16 dims x 4 pieces then are free of bank conflicts (c ^ (v / 4) % 4, right for 32 dims x 2 pieces, cost two cycles
+// a read).  The even and odd steps of a score are chains of their own; their sum also keeps the maximum, which is
+// assembly, from reading a matrix result directly (the compiler does not wait for one there).
+// 16 / 8 heads, us by 32 rows a wave and now, in turn on one card: second pieces of 4 prompts of up to 1500 positions on up to 600
+// cached, window 1024, image block 152 -> 134; 4 x 2000 186 -> 178; 8 x 1500 on 1000, window 1024 294 -> 280; 1 x 2048 on 6000
+// 269 -> 263; 1 x 1000 40.5 -> 37.5; 300 on 1500 64.7 -> 60.4; 100 rows 10.9 -> 9.5; one row on 3000 cached ones 86 -> 65.  Tried: two waves that
+// share 32 rows and exchange halves of the scores, a barrier a block (4 to 12 % slower than 32 rows a wave); four waves and half the
+// ring, two workgroups a compute unit (25 to 60 % slower); requests spread over the matrix instructions (level); all of a block's keys
+// ahead (spills).
+// ---------------------------------------------------------------------------
+constexpr int kPf16Waves = 8, kPf16Threads = kPf16Waves * kWave;
+template <int D>
+constexpr size_t pf16_lds_bytes() { return (size_t)4 * 2 * kPfBlk * D * sizeof(bf16_t); }
+
+template <int D, bool DIRECT>
+__global__ __launch_bounds__(kPf16Threads)
+void prefill_attention_rows16_kernel(PrefillParams p) {
+    constexpr int KS = D / 32, NT = D / 16, BP = D * 4;      // BP: 16-byte pieces of a block's keys (or values)
+    constexpr int NL = BP / kPf16Threads;                               // requests a lane makes for a block's keys (and values)
+    constexpr int WROWS = 16 * kPf16Waves;
+    const int pair = blockIdx.x, b = pair / p.n_kv, g = pair % p.n_kv;
+    const int tile = p.n_tiles - 1 - (int)blockIdx.y;                 // the longest key ranges are started first
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int lr = lane % 16, lc = lane / 16;
+    const int G = p.n_q / p.n_kv;
+    const int L = cached_rows(p.kv_len[b], p.l_max);
+    int n = p.n_new[b]; n = n < 0 ? 0 : (n > p.Lq ? p.Lq : n);
+    if (L + n > p.l_max) n = p.l_max - L > 0 ? p.l_max - L : 0;
+    const int rows = n * G;
+    const int w0 = tile * WROWS;                                      // first stacked row of the workgroup
+    if (w0 >= rows) return;                                           // uniform over the workgroup
+    const int total = L + n;
+    const int m_bidir = p.n_bidir ? p.n_bidir[b] : 0;
+    const int W = p.window;
+    const size_t bg = (size_t)b * p.n_kv + g;
+
+    // rows of this wave (one past the last row repeats it and is not stored) and the keys they see
+    const int r0 = w0 + wave * 16;
+    auto pos_of = [&](int r) { return (r < rows ? r : rows - 1) / G; };
+    const int min_hi = pf_hi(L + pos_of(r0), m_bidir, total), max_hi = pf_hi(L + pos_of(r0 + 15), m_bidir, total);
+    const int min_lo = pf_lo(L + pos_of(r0), W), max_lo = pf_lo(L + pos_of(r0 + 15), W);
+    // blocks of this wave, none where it has no row (it brings its share of the workgroup's blocks in all the same)
+    const int blk_first = min_lo / kPfBlk, blk_last = r0 < rows ? (max_hi - 1) / kPfBlk : -1;
+    // blocks of the workgroup (visibility moves up with the row)
+    const int blk_begin = pf_lo(L + pos_of(w0), W) / kPfBlk;
+    const int blk_end = (pf_hi(L + pos_of(w0 + WROWS - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
+
+    extern __shared__ bf16x8 pf_lds[];                                // [4][keys | values][BP]
+    const bf16_t* const kc = p.kc + bg * (size_t)p.l_max * D + tid * 8;
+    const bf16_t* const vc = p.vc + bg * (size_t)p.l_max * D + (tid ^ ((-(tid / 16)) & 3)) * 8;
+    auto bring = [&](const bf16_t* src, bf16x8* dst) {
+        if constexpr (DIRECT)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+        else
+            dst[lane] = *reinterpret_cast<const bf16x8_any*>(src);
+    };
+    auto request = [&](int blk) {
+        bf16x8* dst = pf_lds + (size_t)(blk % 4) * 2 * BP + wave * kWave;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) bring(kc + ((size_t)blk * BP + u * kPf16Threads) * 8, dst + u * kPf16Threads);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) bring(vc + ((size_t)blk * BP + u * kPf16Threads) * 8, dst + BP + u * kPf16Threads);
+    };
+    request(blk_begin);
+    if (blk_begin + 1 < blk_end) request(blk_begin + 1);
+
+    bf16x8 qreg[KS];
+    int hi_row, lo_row;
+    {
+        const int r = r0 + lr < rows ? r0 + lr : rows - 1;
+        const int i = r / G, qh = r % G;
+        hi_row = pf_hi(L + i, m_bidir, total);
+        lo_row = pf_lo(L + i, W);
+        const bf16_t* qr = p.q + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 32 + lc * 8);
+    }
+    const bf16x8* const kfrag = pf_lds + lane;                        // operand (t, ks) of a block: 64 pieces in lane order
+    const bf16x8* const vfrag = pf_lds + BP + lr * 4 + (lc ^ ((-(lr / 4)) & 3));
+
+    floatx4 acc[NT];
+    bf16x8 ka[KS / 2][2];                          // the first half of the next block's keys
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    constexpr float kLazy = 8.0f;                  // a row's reference exponent is raised only when exceeded by 2^8
+
+    for (int blk0 = blk_begin; blk0 < blk_end; blk0 += 2) {
+        // these two blocks have landed for every wave and everybody is done with the two before, whose places take the next
+        if constexpr (DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const int first = blk0 > blk_first ? blk0 : blk_first, last = blk0 + 1 < blk_last ? blk0 + 1 : blk_last;
+        for (int blk = blk0; blk <= blk0 + 1; ++blk)
+            if (blk + 2 < blk_end) request(blk + 2);
+        if (first > last) continue;
+        {
+            const bf16x8* kp = kfrag + (first % 4) * 2 * BP;
+#pragma unroll
+            for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kp[ks * 64]; ka[ks][1] = kp[(KS + ks) * 64]; }
+        }
+        for (int blk = first; blk <= last; ++blk) {
+            const bf16x8* kp = kfrag + (blk % 4) * 2 * BP;
+            const bf16x8* vp = vfrag + (blk % 4) * 2 * BP;
+            bf16x8 kb[KS / 2][2];
+            floatx4 s[2][2];                       // [keys 8 lc + 4 t + (0..3)][even, odd steps] of row lr
+#pragma unroll
+            for (int ks = 0; ks < KS / 2; ++ks) { kb[ks][0] = kp[(KS / 2 + ks) * 64]; kb[ks][1] = kp[(KS + KS / 2 + ks) * 64]; }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    s[t][ks % 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ks < KS / 2 ? ka[ks % (KS / 2)][t] : kb[ks % (KS / 2)][t], qreg[ks],
+                                                                         ks < 2 ? floatx4{0.f, 0.f, 0.f, 0.f} : s[t][ks % 2], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            bf16x8 v0[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) v0[nt] = vp[nt * 64];
+            __builtin_amdgcn_s_setprio(1);
+            const floatx4 a0 = s[0][0] + s[0][1], a1 = s[1][0] + s[1][1];
+            float sv[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+            if ((blk + 1) * kPfBlk > min_hi || blk * kPfBlk < max_lo) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int key = blk * kPfBlk + lc * 8 + e;
+                    if (key >= hi_row || key < lo_row) sv[e] = -INFINITY;
+                }
+                if ((blk + 1) * kPfBlk > total) {  // values of rows past the valid ones may hold anything
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (blk * kPfBlk + lc * 8 + e >= total) v0[nt][e] = (bf16_t)0.f;
+                }
+            }
+            float mx = pf_max3(pf_max3(sv[0], sv[1], sv[2]), pf_max3(sv[3], sv[4], sv[5]), pf_max3(sv[6], sv[7], sv[7]));
+            mx *= p.scale_log2;
+            if (__any(mx > m_run + kLazy)) {
+                mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+                if (mx > m_run + kLazy) {
+                    const float alpha = __builtin_amdgcn_exp2f(m_run - mx);     // m_run = -inf gives 0
+                    l_run *= alpha;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) acc[nt] *= alpha;
+                    m_run = mx;
+                }
+            }
+            const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+            bf16x8 pv;
+            float ps = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float pe = __builtin_amdgcn_exp2f(fmaf(sv[e], p.scale_log2, neg_m));
+                ps += pe;
+                pv[e] = (bf16_t)pe;
+            }
+            l_run += ps;
+            __builtin_amdgcn_s_setprio(0);
+            if (blk < last) {
+                const bf16x8* kn = kfrag + ((blk + 1) % 4) * 2 * BP;
+#pragma unroll
+                for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kn[ks * 64]; ka[ks][1] = kn[(KS + ks) * 64]; }
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v0[nt], pv, acc[nt], 0, 0, 0);
+            }
+        }
+    }
+
+    // ---- write this wave's rows: lane holds dims 16 nt + 4 lc + (0..3) of row lr ----
+    float l = l_run + __shfl_xor(l_run, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+    const int r = r0 + lr;
+    if (r >= rows) return;
+    const float inv = 1.0f / l;                    // every row sees at least its own key
+    const int i = r / G, qh = r % G;
+    bf16_t* dst = p.out + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D + lc * 4;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const bf16x4 o = {(bf16_t)(acc[nt][0] * inv), (bf16_t)(acc[nt][1] * inv), (bf16_t)(acc[nt][2] * inv), (bf16_t)(acc[nt][3] * inv)};
+        *reinterpret_cast<bf16x4*>(dst + nt * 16) = o;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // fp32: grid (L_q, n_q, B), 256 threads; keys 256 at a time (thread t scores key t, thread c accumulates column c).
 // Row-major fp32 keys, blocked values.
 // ---------------------------------------------------------------------------
@@ -705,6 +897,30 @@ static int launch_prefill_lds(const massv_attn_desc& a, const PrefillParams& p, 
     return direct ? launch_prefill_lds<D, true>(a, p, st) : launch_prefill_lds<D, false>(a, p, st);
 }
 
+template <int D, bool DIRECT>
+static int launch_prefill16(const massv_attn_desc& a, PrefillParams p, hipStream_t st) {
+    constexpr size_t lds = pf16_lds_bytes<D>();
+    static std::atomic<bool> ready[64];           // zero-initialised; calls may come from several threads
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MASSV_ELAUNCH;
+    if (!ready[dev].load(std::memory_order_acquire)) {
+        if (hipFuncSetAttribute((const void*)prefill_attention_rows16_kernel<D, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return MASSV_ELAUNCH;
+        ready[dev].store(true, std::memory_order_release);
+    }
+    const int rows_max = a.n_query * (a.n_q_heads / a.n_kv_heads), per_wg = kPf16Waves * 16;
+    p.n_tiles = (rows_max + per_wg - 1) / per_wg;
+    if (p.n_tiles > 65535) return MASSV_EUNSUPPORTED;
+    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_rows16_kernel<D, DIRECT>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
+                  dim3(kPf16Threads), lds, st, p);
+    return launch_status();
+}
+template <int D>
+static int launch_prefill16(const massv_attn_desc& a, const PrefillParams& p, hipStream_t st) {
+    const bool direct = ((uintptr_t)p.kc | (uintptr_t)p.vc) % 16 == 0;
+    return direct ? launch_prefill16<D, true>(a, p, st) : launch_prefill16<D, false>(a, p, st);
+}
+
 }  // namespace massv
 
 using namespace massv;
@@ -754,7 +970,7 @@ extern "C" int massv_prefill_attention(const massv_attn_desc* desc, const void* 
     switch (a.head_dim) {
         case 64: return few ? launch_prefill_lds<64>(a, p, st) : launch_prefill<64>(a, p, st);
         case 128: return few ? launch_prefill_lds<128>(a, p, st) : launch_prefill<128>(a, p, st);
-        case 256: return launch_prefill_lds<256>(a, p, st);
+        case 256: return launch_prefill16<256>(a, p, st);
     }
     return MASSV_EUNSUPPORTED;
 }

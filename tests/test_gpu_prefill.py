@@ -135,6 +135,15 @@ def test_rows_and_blocks_through_lds(heads, kv_len, n_new, window, bidir, d):
     run_case(s, kv_len, n_new, [t // 2 for t in total], seed=sum(total), window=window, bidir=bidir)
 
 
+@pytest.mark.parametrize("n_new", [7, 8, 9, 63, 64, 65])
+@pytest.mark.parametrize("kv_len,window", [(0, 0), (25, 0), (57, 0), (120, 40), (150, 40)])
+def test_row_tiles_and_block_pairs_d256(n_new, kv_len, window):
+    """d = 256, two heads stacked: 16 rows a wave (8 positions) and 128 a workgroup (64), and key ranges that begin and end in either
+    half of a pair of blocks, for the workgroup and for its waves."""
+    s = synth.LayerShape(256, 4, 2, 256, 704, 4096, dtype="bf16")
+    run_case(s, [kv_len], [n_new], [min(kv_len, 20)], seed=n_new + kv_len, window=window)
+
+
 @pytest.mark.parametrize("d,heads,n_new", [
     (64, (1, 1), [512] * 129), (64, (7, 1), [292] * 32), (64, (7, 1), [292] * 33),      # 258, 256 and 264 workgroups of 256 rows
     (128, (1, 1), [128] * 256), (128, (1, 1), [128] * 257), (128, (1, 1), [129] * 200),      # 256, 257 and 400 of 128
