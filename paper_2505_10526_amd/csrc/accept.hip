@@ -91,16 +91,10 @@ __device__ inline void wave_argmax(float& m, int& am) {       // result in every
     am = __builtin_amdgcn_readlane(am, kWave - 1);
 }
 
-__global__ __launch_bounds__(kAccThreads)
-void accept_stats_kernel(const float* __restrict__ target, const float* __restrict__ draft,
-                         int n_target_rows, int V, int C, TempScale ts, int greedy, int vec,
-                         RowPartial* __restrict__ part) {
-    const int lane = threadIdx.x % kWave;
-    const int c = blockIdx.x * (kAccThreads / kWave) + threadIdx.x / kWave, r = blockIdx.y;
-    if (c >= C) return;                                      // whole wave leaves together
-    const float* row = (r < n_target_rows) ? target + (size_t)r * V
-                                           : draft + (size_t)(r - n_target_rows) * V;
-    const int base = c * kAccChunk;
+// Maximum, first arg-max and sum of exponentials of chunk c of a row, by one wave.
+__device__ inline void chunk_stats(const float* __restrict__ row, int V, int c, TempScale ts, int greedy, int vec,
+                                   RowPartial* __restrict__ out) {
+    const int lane = threadIdx.x % kWave, base = c * kAccChunk;
     float x[kAccPerLane];
     load_chunk(row, V, base, lane, vec, x);
 
@@ -121,8 +115,34 @@ void accept_stats_kernel(const float* __restrict__ target, const float* __restri
     }
     if (lane == 0) {
         RowPartial p; p.m = m; p.arg = am; p.s = s;
-        part[(size_t)r * C + c] = p;
+        *out = p;
     }
+}
+
+__global__ __launch_bounds__(kAccThreads)
+void accept_stats_kernel(const float* __restrict__ target, const float* __restrict__ draft,
+                         int n_target_rows, int V, int C, TempScale ts, int greedy, int vec,
+                         RowPartial* __restrict__ part) {
+    const int c = blockIdx.x * (kAccThreads / kWave) + threadIdx.x / kWave, r = blockIdx.y;
+    if (c >= C) return;                                      // whole wave leaves together
+    const float* row = (r < n_target_rows) ? target + (size_t)r * V
+                                           : draft + (size_t)(r - n_target_rows) * V;
+    chunk_stats(row, V, c, ts, greedy, vec, part + (size_t)r * C + c);
+}
+
+// The norm of the rows that the vocabulary projection reads (the first M workgroups) and pass 1 over the draft rows, which does
+// not wait for the projection: as launches of their own, one ahead of it and one behind, 4.7 and 7.7 us of the sampling call at 8 x 5
+// drafts, each with most of the chip idle or starting up.
+__global__ __launch_bounds__(kNormPackThreads)
+void norm_draft_stats_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ g, bf16_t* __restrict__ y, int M, int H,
+                             float eps, const float* __restrict__ draft, int n_rows, int V, int C, TempScale ts, int vec,
+                             RowPartial* __restrict__ part) {
+    if ((int)blockIdx.x < M) {
+        rmsnorm_pack_row(x, g, y, H, eps, (M + 15) / 16, blockIdx.x);
+        return;
+    }
+    const int w = (blockIdx.x - M) * (kNormPackThreads / kWave) + threadIdx.x / kWave, r = w / C, c = w % C;
+    if (r < n_rows) chunk_stats(draft + (size_t)r * V, V, c, ts, 0, vec, part + (size_t)r * C + c);
 }
 
 constexpr int kDecideThreads = 1024;                      // 16 waves: one row of the sequence each
@@ -557,8 +577,8 @@ extern "C" int massv_spec_accept_static(const float* target_logits, const float*
 }
 
 namespace massv {
-// Target statistics come with the logits (one partial per row and workgroup of the vocabulary projection): pass 1
-// streams the draft rows only; the rest of the call is the same four-kernel chain.
+// Target statistics come with the logits (one partial per row and workgroup of the vocabulary projection), those of the draft
+// rows were formed ahead of it; the rest of the call is the chain of spec_accept.
 struct PrestatsLayout { size_t part_d, sel, mass, total; };
 static PrestatsLayout prestats_layout(int B, int gamma, int V) {
     PrestatsLayout l;
@@ -570,6 +590,17 @@ static PrestatsLayout prestats_layout(int B, int gamma, int V) {
     return l;
 }
 size_t accept_prestats_bytes(int B, int gamma, int V) { return prestats_layout(B, gamma, V).total; }
+
+int launch_norm_draft_stats(const void* x, const void* g, void* y, int M, int H, float eps, const float* draft_logits,
+                            float temperature, int B, int gamma, int V, void* workspace, hipStream_t st) {
+    if (gamma == 0) return launch_rmsnorm_packed(x, g, y, M, H, eps, st);
+    const int C = n_chunks(V), per = kNormPackThreads / kWave;
+    const int vec = (V % 4 == 0) && ((uintptr_t)draft_logits % 16 == 0);
+    launch_traced(MASSV_K_ACCEPT_STATS, norm_draft_stats_kernel, dim3(M + (B * gamma * C + per - 1) / per), dim3(kNormPackThreads), 0, st,
+                  (const bf16_t*)x, (const bf16_t*)g, (bf16_t*)y, M, H, eps, draft_logits, B * gamma, V, C, temp_scale(temperature), vec,
+                  (RowPartial*)((char*)workspace + prestats_layout(B, gamma, V).part_d));
+    return launch_status();
+}
 
 int launch_accept_prestats(const float* target_logits, const RowPartial* part_t, int C_t, const float* draft_logits,
                            const int32_t* draft_tokens, const float* uniforms, float temperature, int B, int gamma, int V,
@@ -583,9 +614,6 @@ int launch_accept_prestats(const float* target_logits, const RowPartial* part_t,
     const TempScale ts = temp_scale(temperature);
     const int vec = (V % 4 == 0) && ((uintptr_t)target_logits % 16 == 0) && (gamma == 0 || (uintptr_t)draft_logits % 16 == 0);
     const int wpb = kAccThreads / kWave;
-    if (gamma > 0)
-        launch_traced(MASSV_K_ACCEPT_STATS, accept_stats_kernel, dim3((C + wpb - 1) / wpb, B * gamma), dim3(kAccThreads), 0, st,
-                      (const float*)nullptr, draft_logits, 0, V, C, ts, 0, vec, part_d);
     hipLaunchKernelGGL(accept_decide_kernel, dim3(B), dim3(kDecideThreads), 0, st,
                        target_logits, draft_logits, draft_tokens, uniforms, B, gamma, V, ts.inv, ts.hi, 0,
                        part_t, C_t, (const RowPartial*)part_d, C, sel, n_accepted, out_tokens);

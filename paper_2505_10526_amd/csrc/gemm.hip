@@ -377,21 +377,27 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     const int hl = seg == 0 ? head : seg == 1 ? head - n_q : head - n_q - n_kv;
     const size_t row0 = (size_t)hl * d + j;
     const float* const w[2] = {mats.w[seg] + row0 * K, mats.w[seg] + (row0 + half) * K};
+    // what the lane's row needs besides the products does not wait for them
+    const int m = m0 + lane;
+    const bool live = lane < kF32Rows && m < M;
+    const int b = live ? m / Q : 0, i = live ? m % Q : 0;
+    const int cached = kv_len[b];
+    const float b1 = mats.bias[seg] ? mats.bias[seg][row0] : 0.f, b2 = mats.bias[seg] ? mats.bias[seg][row0 + half] : 0.f;
+    double sn = 0.0, cs = 1.0;
+    if (seg < 2) {
+        const double ang = (double)pos[live ? m : 0] * exp2(-2.0 * (double)j / (double)d * log2_theta);
+        sincos(ang, &sn, &cs);
+    }
     float acc[2][kF32Rows];
     rows_dot<VEC, 2, true, kF32Rows>(x, w, g, eps, m0, M, K, acc);
     float x1 = acc[0][0], x2 = acc[1][0];
 #pragma unroll
     for (int r = 1; r < kF32Rows; ++r)
         if (lane == r) { x1 = acc[0][r]; x2 = acc[1][r]; }
-    const int m = m0 + lane;
-    if (lane >= kF32Rows || m >= M) return;
-    if (mats.bias[seg]) { x1 += mats.bias[seg][row0]; x2 += mats.bias[seg][row0 + half]; }
-    const int b = m / Q, i = m % Q;
-    const int row = cached_rows(kv_len[b], l_max) + i;
+    if (!live) return;
+    x1 += b1; x2 += b2;
+    const int row = cached_rows(cached, l_max) + i;
     if (seg < 2) {
-        const double ang = (double)pos[m] * exp2(-2.0 * (double)j / (double)d * log2_theta);
-        double sn, cs;
-        sincos(ang, &sn, &cs);
         const float y1 = (float)((double)x1 * cs - (double)x2 * sn);
         const float y2 = (float)((double)x2 * cs + (double)x1 * sn);
         if (seg == 0) {

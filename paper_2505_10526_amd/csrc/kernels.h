@@ -26,6 +26,41 @@ inline void launch_traced(int kid, K kernel, dim3 grid, dim3 block, size_t lds, 
 }
 
 // ---- small row-wise kernels (elementwise.hip) ----
+// Row m of X -> RMSNorm -> operand-order output (see packed_index), by a workgroup of kNormPackThreads; g == nullptr: no
+// normalisation, the row is only re-laid out.  H % 8 == 0.
+constexpr int kNormPackThreads = 1024;
+__device__ inline void rmsnorm_pack_row(const bf16_t* __restrict__ x, const bf16_t* __restrict__ g, bf16_t* __restrict__ y,
+                                        int H, float eps, int mt_count, int m) {
+    const int tid = threadIdx.x;
+    const bf16x8* xr = reinterpret_cast<const bf16x8*>(x + (size_t)m * H);
+    const int groups = H / 8;
+    float rstd = 1.f;
+    if (g) {
+        float ss = 0.f;
+        for (int k8 = tid; k8 < groups; k8 += kNormPackThreads) {
+            const bf16x8 v = xr[k8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { const float f = (float)v[e]; ss += f * f; }
+        }
+        ss = wave_sum(ss);
+        __shared__ float part[16];
+        if ((tid & 63) == 0) part[tid >> 6] = ss;
+        __syncthreads();
+        float tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) tot += part[w];
+        rstd = 1.0f / sqrtf(tot / (float)H + eps);
+    }
+    for (int k8 = tid; k8 < groups; k8 += kNormPackThreads) {
+        bf16x8 v = xr[k8];
+        if (g) {
+            const bf16x8 gv = reinterpret_cast<const bf16x8*>(g)[k8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (bf16_t)((float)v[e] * rstd * (float)gv[e]);
+        }
+        *reinterpret_cast<bf16x8*>(y + packed_index(m, k8 * 8, mt_count)) = v;
+    }
+}
 // bf16 only: y[m,:] = x[m,:] * g / sqrt(mean(x[m,:]^2) + eps), output in operand order (packed_index); g == nullptr re-lays the rows out without normalising.
 int launch_rmsnorm_packed(const void* x, const void* g, void* y, int M, int H, float eps, hipStream_t st);
 // Rotates the q and k heads of qkv[M][(n_q+2n_kv)*d] by pos[m], writes q to
@@ -76,8 +111,11 @@ int launch_accept_decide_greedy(const RowPartial* part, int C, const int32_t* dr
 struct TempScale { float hi, lo; double inv; };
 TempScale temp_scale(float temperature);
 // The accept rule at T > 0 with the target rows' statistics already formed by the vocabulary projection
-// (part_t[B*(gamma+1)][C_t], written by an EPI_LOGITS_STATS launch): pass 1 runs over the draft rows only.
-// ws: accept_prestats_bytes(B, gamma, V) bytes.
+// (part_t[B*(gamma+1)][C_t], written by an EPI_LOGITS_STATS launch).  Pass 1, over the draft rows only, goes out ahead of the
+// projection with the norm of its rows (launch_norm_draft_stats: launch_rmsnorm_packed and pass 1 in one launch).
+// ws: accept_prestats_bytes(B, gamma, V) bytes, the same for both.
+int launch_norm_draft_stats(const void* x, const void* g, void* y, int M, int H, float eps, const float* draft_logits,
+                            float temperature, int B, int gamma, int V, void* ws, hipStream_t st);
 size_t accept_prestats_bytes(int B, int gamma, int V);
 int launch_accept_prestats(const float* target_logits, const RowPartial* part_t, int C_t, const float* draft_logits,
                            const int32_t* draft_tokens, const float* uniforms, float temperature, int B, int gamma, int V,

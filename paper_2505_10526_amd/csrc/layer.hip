@@ -309,7 +309,7 @@ extern "C" int massv_lm_head_greedy_accept(const void* x, const void* final_norm
 // lm_head and the accept rule in one call at any temperature.  T = 0: the greedy path above (no logits written).
 // T > 0: the projection writes the logits (the accept rule gathers p(x_i) from them and re-reads one row per sequence
 // for the final draw) and its epilogue leaves, per row and workgroup, the largest logit, its column and the sum of
-// exponentials -- the target half of the accept call's first pass, which then streams the draft rows only.
+// exponentials -- the target half of the accept call's first pass; the draft half goes out with the norm ahead of the projection.
 static GemmArgs stats_gemm(int32_t M, int32_t H, int32_t V, float temperature) {
     GemmArgs g = {};
     g.n[0] = V; g.M = M; g.K = H; g.epilogue = EPI_LOGITS_STATS; g.dtype = MASSV_BF16; g.kid = MASSV_K_LMHEAD;
@@ -344,12 +344,12 @@ extern "C" int massv_lm_head_accept(const void* x, const void* final_norm, const
     if (!(norm_eps >= 0.f)) return MASSV_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     const int M = B * (gamma + 1);
-    if ((rc = launch_rmsnorm_packed(x, final_norm, workspace, M, H, norm_eps, st)) != MASSV_OK) return rc;
     GemmArgs g = stats_gemm(M, H, V, temperature);
     char* ws = (char*)workspace;
     RowPartial* part = (RowPartial*)(ws + align_up(packed_elems(M, H) * 2, 256));
     const int pieces = gemm_row_pieces(g);
     void* accept_ws = (char*)part + align_up((size_t)M * pieces * sizeof(RowPartial), 256);
+    if ((rc = launch_norm_draft_stats(x, final_norm, workspace, M, H, norm_eps, draft_logits, temperature, B, gamma, V, accept_ws, st)) != MASSV_OK) return rc;
     g.x = workspace; g.w[0] = w_lm; g.y = logits; g.stats = part;
     if ((rc = launch_gemm(g, st)) != MASSV_OK) return rc;
     return launch_accept_prestats(logits, part, pieces, draft_logits, draft_tokens, uniforms, temperature, B, gamma, V,
