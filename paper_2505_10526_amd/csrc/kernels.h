@@ -182,11 +182,11 @@ __device__ inline float row_rstd(const RowScale& r, const float* s_ss, int m) {
     for (int w = 1; w < T / 16; ++w) t += s_ss[w * MT * 16 + m];
     return row_rstd_of(r, t);
 }
-template <int T>
+template <int T, int MT>
 __device__ inline float row_rstd_by16(const RowScale& r, const float* s_ss, int m, int c) {
-    float t = s_ss[c * 16 + m];
+    float t = s_ss[c * MT * 16 + m];
 #pragma unroll
-    for (int w = 16; w < T / 16; w += 16) t += s_ss[(w + c) * 16 + m];
+    for (int w = 16; w < T / 16; w += 16) t += s_ss[(w + c) * MT * 16 + m];
     t += row_ror<8>(t); t += row_ror<4>(t); t += row_ror<2>(t); t += row_ror<1>(t);      // (the same sum in every lane)
     return row_rstd_of(r, t);
 }
@@ -206,9 +206,10 @@ __device__ inline float gemm_act(float x, int act) {
 // Whether the projection (GemmArgs as for launch_gemm) is faster this way than as launch_gemm runs it.
 bool whole_qkv_pays(const GemmArgs& g);
 bool whole_residual_pays(const GemmArgs& g);
-// launch_gemm + launch_qkv_finish in one launch (g.bias: nullptr = none); no head norms.
-int launch_whole_qkv(const GemmArgs& g, const RowScale& scale, const int32_t* pos, const int32_t* kv_len, void* q_out,
-                     void* k_cache, void* v_cache, const massv_attn_desc& a, float theta, hipStream_t st);
+// launch_gemm + launch_qkv_finish in one launch (g.bias: nullptr = none); no head norms.  raw_x != nullptr: also the norm ahead of
+// them, of the row-major rows raw_x with these gains (scale: H and eps; g.x is not read).
+int launch_whole_qkv(const GemmArgs& g, const RowScale& scale, const void* raw_x, const void* gain, const int32_t* pos,
+                     const int32_t* kv_len, void* q_out, void* k_cache, void* v_cache, const massv_attn_desc& a, float theta, hipStream_t st);
 // launch_gemm + launch_residual_finish (without a post norm) in one launch, except that xn_packed receives rows * ln and
 // ss[whole_residual_parts][16 ceil(M/16)] the sums of squares (both only when ln != nullptr).
 int launch_whole_residual(const GemmArgs& g, const void* x_in, const float* h_in, void* x_out, float* h_out, const void* ln,

@@ -147,14 +147,17 @@ static int run_layer(const massv_layer_desc* desc, const massv_layer_weights* w,
     // bf16: the narrow projections leave fp32 partial sums per K slab; the row-wise kernel that has to
     // run next anyway (rotary + append, residual + norm) sums them.
     const size_t wq = (size_t)(a.n_q_heads + 2 * a.n_kv_heads) * a.head_dim;
-    if (!xn_ready && (rc = launch_rmsnorm_packed(x, w->ln1, ws + lay.xn, M, H, desc->norm_eps, st)) != MASSV_OK) return rc;
     const WholeProjs whole = whole_projs(g, w);
-    const RowScale normalised = {};
+    const RowScale normalised = {}, unscaled = {nullptr, 0, H, desc->norm_eps};
+    // up to 16 rows the q/k/v projection normalises the layer's input itself (us a call, norm apart and in it: 1.5B shape, 8 rows 39.2
+    // and 36.9; 7B, 6 rows 104.6 and 103.2; more rows are too much arithmetic for it: 48 rows 127.5 and 137)
+    const bool raw = !xn_ready && whole.qkv && M <= 16;
+    if (!xn_ready && !raw && (rc = launch_rmsnorm_packed(x, w->ln1, ws + lay.xn, M, H, desc->norm_eps, st)) != MASSV_OK) return rc;
     RowScale sums = {partial, whole_residual_parts(g.op), H, desc->norm_eps};      // (no slabs are alive while these are)
     if (whole.qkv) {
         if (bias) { g.qkv.bias[0] = w->bq; g.qkv.bias[1] = w->bk; g.qkv.bias[2] = w->bv; }
-        if ((rc = launch_whole_qkv(g.qkv, xn_ready && xn_scale ? *xn_scale : normalised, pos, kv_len, ws + lay.qrot, k_cache, v_cache, a,
-                                   desc->rope_theta, st)) != MASSV_OK) return rc;
+        if ((rc = launch_whole_qkv(g.qkv, raw ? unscaled : xn_ready && xn_scale ? *xn_scale : normalised, raw ? x : nullptr, w->ln1,
+                                   pos, kv_len, ws + lay.qrot, k_cache, v_cache, a, desc->rope_theta, st)) != MASSV_OK) return rc;
     } else {
         if ((rc = launch_gemm(g.qkv, st)) != MASSV_OK) return rc;
         if ((rc = launch_qkv_finish(partial, gemm_plan(g.qkv).slabs, Mp * wq, bias ? w->bq : nullptr, bias ? w->bk : nullptr,

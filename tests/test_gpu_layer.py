@@ -581,6 +581,31 @@ def test_projections_with_what_follows(name, B, Q):
     run_stack(s, 2, B, Q, rng.integers(1, 60, B), rng.integers(0, 2, B), seed=40 + B, w_std=min(0.05, s.hidden ** -0.5))
 
 
+@pytest.mark.parametrize("name", WHOLE_SHAPES)
+def test_norm_inside_the_query_projection(name):
+    """Up to 16 rows the projection normalises its rows as it reads them, 17 rows have a launch for it: rows of very different size
+    give the same bits in a batch and alone, and the same as rows of 2^k times the size (eps apart)."""
+    s = WHOLE_SHAPES[name]
+    w = binding.pack_layer_weights({k: (None if v is None else to_dev(v, s.dtype)) for k, v in synth.layer_weights(s, 60, std=0.05).items()})
+    cfg = cfg_of(s)
+    cfg.norm_eps = 0.0
+    n, lm = 16, 32
+    x = to_dev(synth.hidden_states(s, n, 1, 61), "bf16") * (2.0 ** torch.arange(n, device=DEV).sub(8)).view(n, 1, 1).to(torch.bfloat16)
+    pos, kv_len = i32(np.zeros((n, 1))), i32(np.zeros(n))
+
+    def keys(rows, scale):
+        k = torch.zeros(rows.stop - rows.start, s.n_kv_heads, lm, s.head_dim, dtype=torch.bfloat16, device=DEV)
+        v = torch.zeros(rows.stop - rows.start, s.n_kv_heads, lm // 32, s.head_dim, 32, dtype=torch.bfloat16, device=DEV)
+        binding.verify_layer(cfg, w, (x[rows] * scale).contiguous(), pos[rows], k, v, kv_len[rows])
+        return k, v
+
+    whole = keys(slice(0, n), 1.0)
+    for rows in (slice(0, 1), slice(3, 12)):
+        assert all(torch.equal(a[rows], b) for a, b in zip(whole, keys(rows, 1.0)))
+    assert all(torch.equal(a, b) for a, b in zip(whole, keys(slice(0, n), 16.0)))
+    assert whole[0].abs().sum() > 0
+
+
 @pytest.mark.parametrize("mlp", [32, 2080, 4128, 6176, 8224, 10272, 12320, 16384, 16416])
 def test_gated_projection_tiles(mlp):
     """1 to 8 tiles a workgroup of the gate / up projection, the last one missing in some workgroups, and one width past them."""
