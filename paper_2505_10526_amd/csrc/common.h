@@ -128,6 +128,28 @@ __device__ inline T wave_scan_incl(T v) {
 }
 __device__ inline float wave_sum(float v) { return lane_value(wave_scan_incl(v), kWave - 1); }
 __device__ inline double wave_sum(double v) { return lane_value(wave_scan_incl(v), kWave - 1); }
+// Eight sums at once: lane l gets the sum over the wave of v[l % 8].  Each of the first three steps halves the values a lane
+// carries (lanes whose bit is clear keep the lower half and hand the upper one to the lane across), so eight values cost 21
+// instructions where eight wave_sum take 64; what is left is summed over the eight groups of lanes.
+__device__ inline float wave_sum8(const float (&v)[8]) {
+    const int lane = threadIdx.x % kWave;
+    float a[4], b[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                              // across: lane l ^ 7
+        const float keep = lane & 4 ? v[4 + i] : v[i], give = lane & 4 ? v[i] : v[4 + i];
+        a[i] = keep + dpp_move<0x141, 0xf>(give, 0.f);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {                              // l ^ 2
+        const float keep = lane & 2 ? a[2 + i] : a[i], give = lane & 2 ? a[i] : a[2 + i];
+        b[i] = keep + dpp_move<0x4e, 0xf>(give, 0.f);
+    }
+    const float keep = lane & 1 ? b[1] : b[0], give = lane & 1 ? b[0] : b[1];
+    float s = keep + dpp_move<0xb1, 0xf>(give, 0.f);           // l ^ 1
+    s += row_ror<8>(s);
+    s += __shfl_xor(s, 16, kWave);
+    return s + __shfl_xor(s, 32, kWave);
+}
 __device__ inline float wave_max(float v) {                   // a lane without a source combines with itself
     v = fmaxf(v, dpp_move<kDppShr1, 0xf>(v, v));
     v = fmaxf(v, dpp_move<kDppShr2, 0xf>(v, v));

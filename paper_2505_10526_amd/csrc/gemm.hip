@@ -263,7 +263,8 @@ __device__ inline float dot_step(float a, float b, float c) { return fmaf(a, b, 
 __device__ inline float dot_step(floatx4_any a, floatx4_any b, float c) { return fmaf(a[3], b[3], fmaf(a[2], b[2], fmaf(a[1], b[1], fmaf(a[0], b[0], c)))); }
 template <typename V> __device__ inline V scale_by(V a, V b) { return a * b; }
 
-// acc[i][r] = sum_k w[i][k] g[k] x[m0 + r][k] / rms(x[m0 + r]) (NORM), or without g and rms; every lane gets the sums.
+// acc[i][r] = sum_k w[i][k] g[k] x[m0 + r][k] / rms(x[m0 + r]) (NORM), or without g and rms.  Eight rows: lane l gets
+// the sums of row l % 8, in acc[i][0]; fewer: every lane gets all of them.
 // Rows past M repeat the last one.  K % VEC == 0.
 template <int VEC, int NW, bool NORM, int R>
 __device__ inline void rows_dot(const float* __restrict__ x, const float* const (&w)[NW], const float* __restrict__ g, float eps,
@@ -313,12 +314,19 @@ __device__ inline void rows_dot(const float* __restrict__ x, const float* const 
     if (k0 + 2 * kWave < kv) steps(k0, std::integral_constant<int, 3>{});
     else if (k0 + kWave < kv) steps(k0, std::integral_constant<int, 2>{});
     else if (k0 < kv) steps(k0, std::integral_constant<int, 1>{});
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
+    if constexpr (R == kF32Rows) {                           // lane l: row l % 8
         float rstd = 1.f;
-        if constexpr (NORM) rstd = 1.0f / sqrtf(wave_sum(ss[r]) / (float)K + eps);
+        if constexpr (NORM) rstd = 1.0f / sqrtf(wave_sum8(ss) / (float)K + eps);
 #pragma unroll
-        for (int i = 0; i < NW; ++i) acc[i][r] = wave_sum(acc[i][r]) * rstd;
+        for (int i = 0; i < NW; ++i) acc[i][0] = wave_sum8(acc[i]) * rstd;
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float rstd = 1.f;
+            if constexpr (NORM) rstd = 1.0f / sqrtf(wave_sum(ss[r]) / (float)K + eps);
+#pragma unroll
+            for (int i = 0; i < NW; ++i) acc[i][r] = wave_sum(acc[i][r]) * rstd;
+        }
     }
 }
 
@@ -335,12 +343,19 @@ void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ g, f
     float acc[1][R];
     rows_dot<VEC, 1, NORM, R>(x, w, g, eps, m0, M, K, acc);
     const float b = mats.bias[seg] ? mats.bias[seg][local] : 0.f;
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (lane == r && m0 + r < M) {
-            const size_t o = (size_t)(m0 + r) * ldy + n;
-            y[o] = acc[0][r] + b + (residual ? residual[o] : 0.f);
+    if constexpr (R == kF32Rows) {
+        if (lane < R && m0 + lane < M) {
+            const size_t o = (size_t)(m0 + lane) * ldy + n;
+            y[o] = acc[0][0] + b + (residual ? residual[o] : 0.f);
         }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (lane == r && m0 + r < M) {
+                const size_t o = (size_t)(m0 + r) * ldy + n;
+                y[o] = acc[0][r] + b + (residual ? residual[o] : 0.f);
+            }
+    }
 }
 
 // act(gate) * up: feature f of both matrices.
@@ -352,10 +367,7 @@ void gated_f32_kernel(const float* __restrict__ x, const float* __restrict__ g, 
     const float* const w[2] = {wg + (size_t)f * K, wu + (size_t)f * K};
     float acc[2][kF32Rows];
     rows_dot<VEC, 2, NORM, kF32Rows>(x, w, g, eps, m0, M, K, acc);
-    float gv = acc[0][0], uv = acc[1][0];
-#pragma unroll
-    for (int r = 1; r < kF32Rows; ++r)
-        if (lane == r) { gv = acc[0][r]; uv = acc[1][r]; }
+    const float gv = acc[0][0], uv = acc[1][0];
     if (lane >= kF32Rows || m0 + lane >= M) return;
     float a;
     if (act == MASSV_ACT_SILU) a = gv / (1.0f + expf(-gv));
@@ -390,12 +402,8 @@ void qkv_rope_f32_kernel(const float* __restrict__ x, const float* __restrict__ 
     }
     float acc[2][kF32Rows];
     rows_dot<VEC, 2, true, kF32Rows>(x, w, g, eps, m0, M, K, acc);
-    float x1 = acc[0][0], x2 = acc[1][0];
-#pragma unroll
-    for (int r = 1; r < kF32Rows; ++r)
-        if (lane == r) { x1 = acc[0][r]; x2 = acc[1][r]; }
     if (!live) return;
-    x1 += b1; x2 += b2;
+    const float x1 = acc[0][0] + b1, x2 = acc[1][0] + b2;
     const int row = cached_rows(cached, l_max) + i;
     if (seg < 2) {
         const float y1 = (float)((double)x1 * cs - (double)x2 * sn);
