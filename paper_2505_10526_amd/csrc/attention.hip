@@ -406,8 +406,8 @@ void attention_mfma_kernel(AttnParams p) {
         const float m_safe = (m == -INFINITY) ? 0.f : m;
         float l = 0.f;
 #pragma unroll
-        for (int w = 0; w < kAttnWaves; ++w) l += s_l[w][r] * exp2f(s_m[w][r] - m_safe);
-        const float f = exp2f(m_run[mt] - m_safe);
+        for (int w = 0; w < kAttnWaves; ++w) l += s_l[w][r] * __builtin_amdgcn_exp2f(s_m[w][r] - m_safe);
+        const float f = __builtin_amdgcn_exp2f(m_run[mt] - m_safe);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] *= f;
         m_tot[mt] = m; l_tot[mt] = l;
@@ -510,12 +510,12 @@ void attention_combine_kernel(const float* __restrict__ part_o, const float* __r
 #pragma unroll
         for (int u = 0; u < SB; ++u) mb = fmaxf(mb, ms[u]);
         if (mb == -INFINITY) continue;               // no split so far saw a visible key for this row
-        const float keep = exp2f(m - mb);             // m = -inf gives 0
+        const float keep = __builtin_amdgcn_exp2f(m - mb);             // m = -inf gives 0
         l *= keep; o *= keep; m = mb;
 #pragma unroll
         for (int u = 0; u < SB; ++u) {
             if (ms[u] == -INFINITY) continue;         // that split's sums may be uninitialised
-            const float w = exp2f(ms[u] - m);
+            const float w = __builtin_amdgcn_exp2f(ms[u] - m);
             l += ls[u] * w;
             o += os[u] * w;
         }
