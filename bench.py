@@ -26,7 +26,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gateup_kernel_hbm_traffic.json")
-KERNEL_SOURCES = ["paper_2505_10526_amd/csrc/gemm.hip", "paper_2505_10526_amd/csrc/common.h",
+KERNEL_SOURCES = ["paper_2505_10526_amd/csrc/gemm.hip", "paper_2505_10526_amd/csrc/gemm_stream.h", "paper_2505_10526_amd/csrc/common.h",
                   "paper_2505_10526_amd/csrc/kernels.h"]
 
 

@@ -100,7 +100,8 @@ static WholeProjs whole_projs(const LayerGemms& g, const massv_layer_weights* w)
 // scale too unless next_scales is set (the next layer's first projection will).  All are bf16-path options.
 static int run_layer(const massv_layer_desc* desc, const massv_layer_weights* w, void* x, const int32_t* pos,
                      void* k_cache, void* v_cache, const int32_t* kv_len, void* workspace,
-                     const LayerLayout& lay, bool xn_ready, const void* next_ln, hipStream_t st, RowScale* xn_scale = nullptr, bool next_scales = false) {
+                     const LayerLayout& lay, bool xn_ready, const void* next_ln, hipStream_t st,
+                     RowScale* xn_scale = nullptr, bool next_scales = false) {
     int rc;
     const massv_attn_desc& a = desc->attn;
     char* ws = (char*)workspace;
@@ -144,8 +145,9 @@ static int run_layer(const massv_layer_desc* desc, const massv_layer_weights* w,
         if (w->post_mlp_norm) return launch_postnorm_residual(x, ws + lay.proj, w->post_mlp_norm, M, H, desc->norm_eps, st);
         return MASSV_OK;
     }
-    // bf16: the narrow projections leave fp32 partial sums per K slab; the row-wise kernel that has to
-    // run next anyway (rotary + append, residual + norm) sums them.
+    // bf16: six launches up to 16 rows, where the projections carry what follows them; otherwise the narrow projections (q/k/v from 49
+    // rows on, O from 33, down from 17, those of layers with head or post norms) leave fp32 partial sums per K slab, and the row-wise
+    // kernel that then has to run (rotary + append, residual + norm) sums them.
     const size_t wq = (size_t)(a.n_q_heads + 2 * a.n_kv_heads) * a.head_dim;
     const WholeProjs whole = whole_projs(g, w);
     const RowScale normalised = {}, unscaled = {nullptr, 0, H, desc->norm_eps};

@@ -13,8 +13,9 @@
 // 14 TB/s together and 60 GB/s each.  Hence 16 waves that take the 32-wide steps of K in turn with all loads of U steps in flight
 // (a workgroup of 4 waves with fewer loads each took one more trip to memory), one round of workgroups, and the rules below on how many
 // rows and features are worth it.  The operand rows past M are not fetched.
-// us of a whole layer, slabs and this, same box: 1.5B shape, 8 rows 48.3 -> 39.5, 16 rows 49.3 -> 45.8; 7B shape, 6 rows
-// 107.5 -> 101.1; 12B shape (no extra norms), 6 rows 105.3 -> 94.8.
+// us a layer in a stack, slabs and this, in turn on one card: 1.5B shape, 8 rows 48.3 -> 39.5, 16 rows 49.3 -> 45.8; 7B shape, 6 rows
+// 107.5 -> 101.1; 12B shape (no extra norms), 6 rows 105.3 -> 94.8.  Launches of the 1.5B shape, 8 rows, before and now: q/k/v 4.4 + 3.9 -> 5.5,
+// O 4.2 + 3.6 -> 4.4, gate / up 13.8 -> 12.9, down 7.3 -> 8.4 with 3.6 behind it before.
 #include "gemm_stream.h"
 
 #include <atomic>
