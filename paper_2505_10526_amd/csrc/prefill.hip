@@ -605,24 +605,29 @@ void prefill_attention_lds_kernel(PrefillParams p) {
 // ---------------------------------------------------------------------------
 // d = 256: 16 rows per wave, eight waves, two a SIMD.  With 32 rows a wave is alone on its SIMD (accumulators and Q take 192
 // registers) and its scores, softmax and second product follow one another; with 16 one wave's softmax, which goes first
-// (s_setprio), runs beside the other's matrix instructions.  Twice the LDS reads for it: 37 % of the cycles instead of 17, at 256 bytes a
-// cycle; matrix cores 34 -> 38 % busy at 2048 positions behind 6000 (the rest: both waves wait for the same fragments behind a
-// barrier).  Blocks come in pairs through a ring of two pairs, one barrier a pair; half of a block's keys are read ahead, behind the
-// second product of the block before.
+// (s_setprio), runs beside the other's matrix instructions, for twice the LDS reads, at 256 bytes a cycle.  What bounds it: both
+// waves of a SIMD wait for the same fragments behind a barrier.  Blocks are taken in pairs, one barrier a pair; half of a block's
+// keys are read ahead, behind the second product of the block before.
+// The blocks travel through a ring of five (all 160 KB): a wave asks for one as it opens a pair and for the next between the
+// two blocks.  With a ring of two pairs and both asked for at once, a request held its wave as long as the memory took to accept it, and
+// all waves stood still together: caches of 1200 rows and more that are not in the last-level cache, tiles of 128 rows, were 3 to 9 %
+// slower than by 32 rows a wave (1 x 64 positions on 6000 211 us; ring of five, both at once 218).
 // Key fragments lie as in the cache, 1 KB each.  Piece c (8 keys) of dim v lies at place c ^ (-(v / 4)) % 4 of the dim's four:
 // a fragment's 16 dims x 4 pieces then are free of bank conflicts (c ^ (v / 4) % 4, right for 32 dims x 2 pieces, cost two cycles
 // a read).  The even and odd steps of a score are chains of their own; their sum also keeps the maximum, which is
 // assembly, from reading a matrix result directly (the compiler does not wait for one there).
-// 16 / 8 heads, us by 32 rows a wave and now, in turn on one card: second pieces of 4 prompts of up to 1500 positions on up to 600
-// cached, window 1024, image block 152 -> 134; 4 x 2000 186 -> 178; 8 x 1500 on 1000, window 1024 294 -> 280; 1 x 2048 on 6000
-// 269 -> 263; 1 x 1000 40.5 -> 37.5; 300 on 1500 64.7 -> 60.4; 100 rows 10.9 -> 9.5; one row on 3000 cached ones 86 -> 65.  Tried: two waves that
-// share 32 rows and exchange halves of the scores, a barrier a block (4 to 12 % slower than 32 rows a wave); four waves and half the
-// ring, two workgroups a compute unit (25 to 60 % slower); requests spread over the matrix instructions (level); all of a block's keys
-// ahead (spills).
+// 16 / 8 heads, caches not in the last-level cache, us by 32 rows a wave, ring of two pairs and now, in turn on one card: second pieces
+// of 4 prompts of up to 1500 positions on up to 600 cached, window 1024, image block 149, 136 and 135; 4 x 2000 171, 159, 158; 8 x 1500
+// on 1000, window 1024 301, 274, 270; 1 x 2048 on 6000 267, 278, 256; 1 x 64 on 6000 197, 212, 184; 1 x 1000 39.8, 36.8, 36.3; 300 on
+// 1500 64.0, 60.8, 58.7; 100 rows 10.7, 9.3, 9.4; one row on 3000 cached ones 88, 73, 72, 16 of them 97, 99, 87.  Over 6600 calls (1 to
+// 4096 rows, caches to 8000, windows, in and out of the last-level cache) none is slower than by 32 rows a wave beyond 1.5 %.  Tried: two
+// waves that share 32 rows and exchange halves of the scores, a barrier a block (4 to 12 % slower than 32 rows a wave); four waves and
+// half the ring, two workgroups a compute unit (25 to 60 % slower); one load a thread that brings the pair after the next as far as L2
+// (up to 25 % slower); places of the ring counted instead of blk % 5 (2 % slower); all of a block's keys ahead (spills).
 // ---------------------------------------------------------------------------
-constexpr int kPf16Waves = 8, kPf16Threads = kPf16Waves * kWave;
+constexpr int kPf16Waves = 8, kPf16Threads = kPf16Waves * kWave, kPf16Ring = 5;
 template <int D>
-constexpr size_t pf16_lds_bytes() { return (size_t)4 * 2 * kPfBlk * D * sizeof(bf16_t); }
+constexpr size_t pf16_lds_bytes() { return (size_t)kPf16Ring * 2 * kPfBlk * D * sizeof(bf16_t); }
 
 template <int D, bool DIRECT>
 __global__ __launch_bounds__(kPf16Threads)
@@ -658,7 +663,7 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
     const int blk_begin = pf_lo(L + pos_of(w0), W) / kPfBlk;
     const int blk_end = (pf_hi(L + pos_of(w0 + WROWS - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
 
-    extern __shared__ bf16x8 pf_lds[];                                // [4][keys | values][BP]
+    extern __shared__ bf16x8 pf_lds[];                                // [kPf16Ring][keys | values][BP]
     const bf16_t* const kc = p.kc + bg * (size_t)p.l_max * D + tid * 8;
     const bf16_t* const vc = p.vc + bg * (size_t)p.l_max * D + (tid ^ ((-(tid / 16)) & 3)) * 8;
     auto bring = [&](const bf16_t* src, bf16x8* dst) {
@@ -667,8 +672,9 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
         else
             dst[lane] = *reinterpret_cast<const bf16x8_any*>(src);
     };
+    auto slot = [&](int blk) { return (int)((unsigned)blk % kPf16Ring) * 2 * BP; };
     auto request = [&](int blk) {
-        bf16x8* dst = pf_lds + (size_t)(blk % 4) * 2 * BP + wave * kWave;
+        bf16x8* dst = pf_lds + slot(blk) + wave * kWave;
 #pragma unroll
         for (int u = 0; u < NL; ++u) bring(kc + ((size_t)blk * BP + u * kPf16Threads) * 8, dst + u * kPf16Threads);
 #pragma unroll
@@ -699,24 +705,28 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
     constexpr float kLazy = 8.0f;                  // a row's reference exponent is raised only when exceeded by 2^8
 
     for (int blk0 = blk_begin; blk0 < blk_end; blk0 += 2) {
-        // these two blocks have landed for every wave and everybody is done with the two before, whose places take the next
-        if constexpr (DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        // these two blocks have landed for every wave (a wave's requests complete in order; the block behind them may still be on
+        // its way) and everybody is done with the two before, whose places take the next
+        if constexpr (DIRECT) {
+            if (blk0 > blk_begin && blk0 + 2 < blk_end) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * NL) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         const int first = blk0 > blk_first ? blk0 : blk_first, last = blk0 + 1 < blk_last ? blk0 + 1 : blk_last;
-        for (int blk = blk0; blk <= blk0 + 1; ++blk)
-            if (blk + 2 < blk_end) request(blk + 2);
+        for (int blk = blk0 + (blk0 > blk_begin ? 3 : 2); blk <= blk0 + 3; ++blk)
+            if (blk < blk_end) request(blk);
+        if (first >= last && blk0 + 4 < blk_end) request(blk0 + 4);
         if (first > last) continue;
         {
-            const bf16x8* kp = kfrag + (first % 4) * 2 * BP;
+            const bf16x8* kp = kfrag + slot(first);
 #pragma unroll
             for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kp[ks * 64]; ka[ks][1] = kp[(KS + ks) * 64]; }
         }
         for (int blk = first; blk <= last; ++blk) {
-            const bf16x8* kp = kfrag + (blk % 4) * 2 * BP;
-            const bf16x8* vp = vfrag + (blk % 4) * 2 * BP;
+            const bf16x8* kp = kfrag + slot(blk);
+            const bf16x8* vp = vfrag + slot(blk);
             bf16x8 kb[KS / 2][2];
             floatx4 s[2][2];                       // [keys 8 lc + 4 t + (0..3)][even, odd steps] of row lr
 #pragma unroll
@@ -774,7 +784,8 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
             l_run += ps;
             __builtin_amdgcn_s_setprio(0);
             if (blk < last) {
-                const bf16x8* kn = kfrag + ((blk + 1) % 4) * 2 * BP;
+                if (blk0 + 4 < blk_end) request(blk0 + 4);
+                const bf16x8* kn = kfrag + slot(blk + 1);
 #pragma unroll
                 for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kn[ks * 64]; ka[ks][1] = kn[(KS + ks) * 64]; }
             }

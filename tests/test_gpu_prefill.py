@@ -128,8 +128,9 @@ def test_bench_shape_sampled_rows():
     ((8, 1), [95, 32], [16, 33], 70, True),       # 128 rows exactly, and one position more
     ((4, 2), [1000, 0], [5, 300], 0, False)])     # many more cached rows than new ones; a short and a long sequence
 def test_rows_and_blocks_through_lds(heads, kv_len, n_new, window, bidir, d):
-    """The kernel of d = 256 and of small launches: row tiles of 32 per wave and 128 per workgroup, rings of four key blocks shared by waves that need
-    different ones; lengths at and around those edges, NaN in every row past the valid ones."""
+    """The kernels that stage blocks in LDS (small launches of d = 64 and 128: 32 rows a wave; d = 256: 16 rows a wave), 128 rows a
+    workgroup and rings of key blocks shared by waves that need different ones; lengths at and around those edges, NaN in every
+    row past the valid ones."""
     s = synth.LayerShape(256, heads[0], heads[1], d, 704, 4096, dtype="bf16")
     total = [a + b for a, b in zip(kv_len, n_new)]
     run_case(s, kv_len, n_new, [t // 2 for t in total], seed=sum(total), window=window, bidir=bidir)
@@ -142,6 +143,27 @@ def test_row_tiles_and_block_pairs_d256(n_new, kv_len, window):
     half of a pair of blocks, for the workgroup and for its waves."""
     s = synth.LayerShape(256, 4, 2, 256, 704, 4096, dtype="bf16")
     run_case(s, [kv_len], [n_new], [min(kv_len, 20)], seed=n_new + kv_len, window=window)
+
+
+@pytest.mark.parametrize("blocks", range(1, 13))
+@pytest.mark.parametrize("n_new,window", [(64, 0), (66, 0), (30, 0), (64, 50)])
+def test_block_ring_d256(blocks, n_new, window):
+    """d = 256: one to twelve blocks through the ring of five, the last one full or begun, all waves with the same blocks (64 positions
+    x 2 heads), one wave of a second workgroup, idle waves, and waves that leave blocks out (window); the same bits from caches that
+    start off a multiple of 16 bytes, which take the other way into LDS."""
+    s = synth.LayerShape(256, 4, 2, 256, 704, 4096, dtype="bf16")
+    for total in (32 * blocks, 32 * blocks - 31):
+        new = min(n_new, total)
+        run_case(s, [total - new], [new], [0], seed=blocks + n_new, window=window)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(total)
+        rn = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+        q, k, v = rn(1, new, 4, 256), rn(1, 2, 32 * blocks, 256), rn(1, 2, blocks, 256, 32)
+        out = []
+        for off in (0, 1):
+            kv = [torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)[off:off + t.numel()].view(t.shape).copy_(t) for t in (k, v)]
+            out.append(binding.prefill_attention(q, kv[0], kv[1], i32([total - new]), i32([new]), window=window))
+        assert torch.equal(out[0], out[1])
 
 
 @pytest.mark.parametrize("d,heads,n_new", [
