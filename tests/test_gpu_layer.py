@@ -581,6 +581,22 @@ def test_projections_with_what_follows(name, B, Q):
     run_stack(s, 2, B, Q, rng.integers(1, 60, B), rng.integers(0, 2, B), seed=40 + B, w_std=min(0.05, s.hidden ** -0.5))
 
 
+# every wave refills its slots: what the widths above, with a step or two a wave, do not reach
+@pytest.mark.parametrize("s,layers,B,Q", [
+    (synth.QWEN1P5B, 2, 8, 1),                                    # down: ten slots, 8 or 9 steps; gate / up 5 tiles, 6 steps
+    (synth.QWEN1P5B, 2, 12, 1), (synth.QWEN1P5B, 2, 16, 1),       # O with four slots, down with eight and 17 or 18 steps
+    (synth.GEMMA12B, 1, 1, 6),                                    # gate / up 8 tiles, 15 steps of four slots; 16 pairs, normalised as they are read
+    (synth.LayerShape(2048, 4, 2, 64, 11008, 4096), 2, 8, 1),     # down: 10 or 11 steps of ten slots
+    (synth.LayerShape(4096, 4, 2, 64, 10208, 4096), 2, 9, 1),     # gate / up 5, 6 and 7 tiles (4 to 6 in some workgroups), 16 steps
+    (synth.LayerShape(4096, 4, 2, 64, 12256, 4096), 1, 2, 4),
+    (synth.LayerShape(4096, 4, 2, 64, 14304, 4096), 1, 4, 4),
+    (synth.LayerShape(4096, 8, 4, 64, 2080, 4096), 2, 8, 3),      # 8 pairs, two and three row tiles, 8 steps
+    (synth.LayerShape(4096, 8, 4, 64, 2080, 4096), 2, 8, 6)], ids=lambda v: f"{v.hidden}x{v.mlp}" if isinstance(v, synth.LayerShape) else str(v))
+def test_projections_with_what_follows_at_size(s, layers, B, Q):
+    rng = np.random.default_rng(B * 10 + Q)
+    run_stack(s, layers, B, Q, rng.integers(1, 60, B), rng.integers(0, 2, B), seed=70 + B, w_std=min(0.02, s.hidden ** -0.5))
+
+
 @pytest.mark.parametrize("name", WHOLE_SHAPES)
 def test_norm_inside_the_query_projection(name):
     """Up to 16 rows the projection normalises its rows as it reads them, 17 rows have a launch for it: rows of very different size
