@@ -597,6 +597,48 @@ def test_projections_with_what_follows_at_size(s, layers, B, Q):
     run_stack(s, layers, B, Q, rng.integers(1, 60, B), rng.integers(0, 2, B), seed=70 + B, w_std=min(0.02, s.hidden ** -0.5))
 
 
+LAYER_KINDS = {"plain": (), "head_norms": ("q_norm", "k_norm"), "query_norm": ("q_norm",), "attention_norm": ("post_attn_norm",),
+               "mlp_norm": ("post_mlp_norm",)}
+
+
+@pytest.mark.parametrize("second", LAYER_KINDS)
+@pytest.mark.parametrize("first", LAYER_KINDS)
+def test_rows_handed_between_layers_of_two_kinds(first, second):
+    """Two layers in one call, each with its own selection of the optional norms: rows normalised by the kernel that closes a layer, or as
+    row * gains with sums of squares, to a q/k/v projection that applies the scale or cannot (head norms), at one, two and three row tiles."""
+    import dataclasses
+    s = dataclasses.replace(synth.TINY_BF16, qk_norm=True, post_norms=True)
+    norms = ("q_norm", "k_norm", "post_attn_norm", "post_mlp_norm")
+    for B, Q in ((5, 1), (3, 4), (4, 6), (8, 5)):
+        seed, ws_h = 80 + B, []
+        for l, kind in enumerate((first, second)):
+            w = synth.layer_weights(s, seed, layer=l, std=0.05)
+            w.update({n: None for n in norms if n not in LAYER_KINDS[kind]})
+            ws_h.append(w)
+        kv_len = np.random.default_rng(seed).integers(1, 60, B)
+        kvs = [synth.kv_cache(s, B, Q, kv_len, np.zeros(B, np.int32), seed, layer=l, hot_keys=1) for l in range(2)]
+        x = synth.hidden_states(s, B, Q, seed)
+        pos = synth.positions(kvs[0].kv_len, kvs[0].n_img, Q)
+        y_ref, refs = x, []
+        for w, kv in zip(ws_h, kvs):
+            y_ref, k_ref, v_ref = O.verify_layer(s, w, y_ref, pos, kv.k, kv.v, kv.kv_len)
+            refs.append((k_ref, v_ref))
+        lm = round_up(kvs[0].l_max, 32)
+        kds = [binding.k_cache_pack(to_dev(pad_rows(kv.k, lm), s.dtype)) for kv in kvs]
+        vds = [binding.v_cache_pack(to_dev(pad_rows(kv.v, lm), s.dtype)) for kv in kvs]
+        wds = [binding.pack_layer_weights({k: (None if v is None else to_dev(v, s.dtype)) for k, v in w.items()}) for w in ws_h]
+        xd = to_dev(x, s.dtype)
+        binding.verify_layers(cfg_of(s), binding.LayerStack(wds, kds, vds), xd, i32(pos), i32(kvs[0].kv_len), lm)
+        torch.cuda.synchronize()
+        assert_close(xd.float().cpu().numpy(), y_ref, TOL_BF16, f"{B * Q} rows, output")
+        for l in range(2):
+            for got, ref, what in zip((k_cache_to_rows(kds[l]), v_blocked_to_rows(vds[l])), refs[l], ("keys", "values")):
+                got = got.float().cpu().numpy()
+                for b in range(B):
+                    L = int(kv_len[b])
+                    assert_close(got[b, :, L:L + Q], ref[b, :, L:L + Q], TOL_BF16, f"{B * Q} rows, layer {l}, appended {what}")
+
+
 @pytest.mark.parametrize("name", WHOLE_SHAPES)
 def test_norm_inside_the_query_projection(name):
     """Up to 16 rows the projection normalises its rows as it reads them, 17 rows have a launch for it: rows of very different size
