@@ -642,26 +642,41 @@ def test_rows_handed_between_layers_of_two_kinds(first, second):
 @pytest.mark.parametrize("name", WHOLE_SHAPES)
 def test_norm_inside_the_query_projection(name):
     """Up to 16 rows the projection normalises its rows as it reads them, 17 rows have a launch for it: rows of very different size
-    give the same bits in a batch and alone, and the same as rows of 2^k times the size (eps apart)."""
+    give the same bits in a batch and alone, and the same as rows of 2^k times the size (eps apart); the keys and values that a call of
+    17 rows appends are the same but for rounding, and both are the checker's."""
     s = WHOLE_SHAPES[name]
-    w = binding.pack_layer_weights({k: (None if v is None else to_dev(v, s.dtype)) for k, v in synth.layer_weights(s, 60, std=0.05).items()})
+    w_h = synth.layer_weights(s, 60, std=0.05)
+    w = binding.pack_layer_weights({k: (None if v is None else to_dev(v, s.dtype)) for k, v in w_h.items()})
     cfg = cfg_of(s)
     cfg.norm_eps = 0.0
     n, lm = 16, 32
-    x = to_dev(synth.hidden_states(s, n, 1, 61), "bf16") * (2.0 ** torch.arange(n, device=DEV).sub(8)).view(n, 1, 1).to(torch.bfloat16)
-    pos, kv_len = i32(np.zeros((n, 1))), i32(np.zeros(n))
+    x_h = synth.hidden_states(s, n + 1, 1, 61) * (2.0 ** (np.arange(n + 1, dtype=np.float32) - 8)).reshape(-1, 1, 1)
+    pos_h = (3 + 7 * np.arange(n + 1)).reshape(-1, 1)
+    x, pos, kv_len = to_dev(x_h, "bf16"), i32(pos_h), i32(np.zeros(n + 1))
 
-    def keys(rows, scale):
+    def keys(rows, scale=1.0):
         k = torch.zeros(rows.stop - rows.start, s.n_kv_heads, lm, s.head_dim, dtype=torch.bfloat16, device=DEV)
         v = torch.zeros(rows.stop - rows.start, s.n_kv_heads, lm // 32, s.head_dim, 32, dtype=torch.bfloat16, device=DEV)
         binding.verify_layer(cfg, w, (x[rows] * scale).contiguous(), pos[rows], k, v, kv_len[rows])
         return k, v
 
-    whole = keys(slice(0, n), 1.0)
+    whole = keys(slice(0, n))
     for rows in (slice(0, 1), slice(3, 12)):
-        assert all(torch.equal(a[rows], b) for a, b in zip(whole, keys(rows, 1.0)))
+        assert all(torch.equal(a[rows], b) for a, b in zip(whole, keys(rows)))
     assert all(torch.equal(a, b) for a, b in zip(whole, keys(slice(0, n), 16.0)))
     assert whole[0].abs().sum() > 0
+
+    import dataclasses
+    zeros = np.zeros((n + 1, s.n_kv_heads, lm, s.head_dim), np.float32)
+    _, k_ref, v_ref = O.verify_layer(dataclasses.replace(s, norm_eps=0.0), w_h, x_h, pos_h, zeros, zeros, np.zeros(n + 1, np.int32))
+    apart = keys(slice(0, n + 1))
+    for got, ref in ((apart, slice(0, n + 1)), (whole, slice(0, n))):
+        assert_close(k_cache_to_rows(got[0]).float().cpu().numpy()[:, :, 0], k_ref[ref, :, 0], TOL_BF16, "keys")
+        assert_close(v_blocked_to_rows(got[1]).float().cpu().numpy()[:, :, 0], v_ref[ref, :, 0], TOL_BF16, "values")
+    # each side rounds the operand of a sum over the inputs (relative 2^-9 at most, at random: 2^-9 / sqrt(3) of the sum's rms, sqrt(2) of that
+    # between the two) and the result (2^-9 of it): five deviations of the first and two roundings stay under 1.2e-2 of the largest value
+    for a, b in zip(whole, apart):
+        assert_close(a.float().cpu().numpy(), b[:n].float().cpu().numpy(), 1.2e-2, "17 rows")
 
 
 @pytest.mark.parametrize("mlp", [32, 2080, 4128, 6176, 8224, 10272, 12320, 16384, 16416])
