@@ -430,7 +430,6 @@ int launch_whole_residual(const GemmArgs& g, const void* x_in, const float* h_in
     // (no more slots than a wave has steps: a small launch mostly waits for its instructions; O of the 1.5B shape 5.2 -> 4.4 us with 4)
     if (whole_eights(g) && g.K <= 64 * kWholeWaves * 4) return launch_whole<1, 4, WHOLE_RES8>(d, g.n[0] / 8, g.kid, st);
     if (whole_eights(g)) return launch_whole<1, 10, WHOLE_RES8>(d, g.n[0] / 8, g.kid, st);
-    if (g.M <= 16 && g.K <= 32 * kWholeWaves * 4) return launch_whole<1, 4, WHOLE_RES16>(d, g.n[0] / 16, g.kid, st);
     if (g.M <= 16) return launch_whole<1, 8, WHOLE_RES16>(d, g.n[0] / 16, g.kid, st);
     return launch_whole<2, 4, WHOLE_RES16>(d, g.n[0] / 16, g.kid, st);
 }
