@@ -477,16 +477,25 @@ int massv_rmsnorm(const void* x, const void* gain, void* y, int32_t M, int32_t H
 /* enabled; the caller synchronises and reads hipEventElapsedTime.             */
 /* kernel_id < 0 disarms.                                                      */
 /* Do not arm while the stream is being captured into a graph.                 */
+/* An id names the launch that does a job; what else rides on that launch      */
+/* depends on the sizes (below, for bf16), so times of one id on either side   */
+/* of such a line are not of the same work.  A request for a launch that a     */
+/* call does not make (ACCEPT_STATS with gamma = 0 in lm_head_accept, the      */
+/* merge of an unsplit attention, the fp32 layer's kernels) stays armed.       */
 /* ------------------------------------------------------------------------- */
 typedef enum {
-    MASSV_K_QKV = 0,          /* fused q/k/v projection of verify_layer */
+    MASSV_K_QKV = 0,          /* q/k/v projection of verify_layer: K slabs, summed by an untimed launch; or, up to 48 rows and 8192
+                                 features without head norms, with bias, rotation and cache append, and up to 16 rows in a call's first layer
+                                 with the norm ahead of it */
     MASSV_K_ATTENTION = 1,    /* the split-KV attention kernel */
     MASSV_K_ATTN_COMBINE = 2, /* merge of the KV splits */
-    MASSV_K_OPROJ = 3,        /* output projection + residual */
-    MASSV_K_GATEUP = 4,       /* gate/up projection + activation */
-    MASSV_K_DOWN = 5,         /* down projection + residual */
-    MASSV_K_LMHEAD = 6,       /* vocabulary projection of lm_head_logits */
-    MASSV_K_ACCEPT_STATS = 7, /* pass 1 of spec_accept over all logit rows */
+    MASSV_K_OPROJ = 3,        /* output projection: K slabs; or, up to 32 rows and 4096 features without a block-output norm, with the
+                                 residual and the gains and sums of squares of the next norm */
+    MASSV_K_GATEUP = 4,       /* gate/up projection + activation (and, behind such an output projection, the rows' scale) */
+    MASSV_K_DOWN = 5,         /* down projection: as the output projection, up to 16 rows */
+    MASSV_K_LMHEAD = 6,       /* vocabulary projection of lm_head_logits, lm_head_greedy_accept and lm_head_accept */
+    MASSV_K_ACCEPT_STATS = 7, /* pass 1 of spec_accept over all logit rows; in lm_head_accept at T > 0 over the draft rows alone, with
+                                 the norm of the projection's rows */
     MASSV_K_RESIDUAL_MASS = 8,/* pass 2 of spec_accept over the resampled rows */
     MASSV_K_LINEAR = 9,       /* the tile kernel of massv_linear */
     MASSV_K_PREFILL_ATTENTION = 10  /* the bf16 kernel of prefill_attention */

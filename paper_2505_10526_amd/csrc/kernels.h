@@ -1,5 +1,5 @@
-// Internal launch interface between the translation units of libmassv_verify.
-// Every function only enqueues on `st` and returns a massv_status.
+// Internal interface between the translation units of libmassv_verify: launches (every launch_* function only enqueues on `st` and
+// returns a massv_status) and the device code that two of them share.
 #pragma once
 
 #include "common.h"

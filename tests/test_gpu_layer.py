@@ -584,7 +584,7 @@ def test_projections_with_what_follows(name, B, Q):
 # every wave refills its slots: what the widths above, with a step or two a wave, do not reach
 @pytest.mark.parametrize("s,layers,B,Q", [
     (synth.QWEN1P5B, 2, 8, 1),                                    # down: ten slots, 8 or 9 steps; gate / up 5 tiles, 6 steps
-    (synth.QWEN1P5B, 2, 12, 1), (synth.QWEN1P5B, 2, 16, 1),       # O with four slots, down with eight and 17 or 18 steps
+    (synth.QWEN1P5B, 2, 12, 1), (synth.QWEN1P5B, 2, 16, 1),       # O and down with eight slots, 3 and 17 or 18 steps
     (synth.GEMMA12B, 1, 1, 6),                                    # gate / up 8 tiles, 15 steps of four slots; 16 pairs, normalised as they are read
     (synth.LayerShape(2048, 4, 2, 64, 11008, 4096), 2, 8, 1),     # down: 10 or 11 steps of ten slots
     (synth.LayerShape(4096, 4, 2, 64, 10208, 4096), 2, 9, 1),     # gate / up 5, 6 and 7 tiles (4 to 6 in some workgroups), 16 steps
