@@ -405,6 +405,8 @@ void attention_mfma_kernel(AttnParams p) {
         for (int w = 1; w < kAttnWaves; ++w) m = fmaxf(m, s_m[w][r]);
         const float m_safe = (m == -INFINITY) ? 0.f : m;
         float l = 0.f;
+        // (the hardware exponential: the library's differs from it only where the result is below 2^-126, which becomes 0; the row's sum holds
+        // the largest wave's own, so such a part is under 2^-100 of it)
 #pragma unroll
         for (int w = 0; w < kAttnWaves; ++w) l += s_l[w][r] * __builtin_amdgcn_exp2f(s_m[w][r] - m_safe);
         const float f = __builtin_amdgcn_exp2f(m_run[mt] - m_safe);

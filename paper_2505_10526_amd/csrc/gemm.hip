@@ -255,7 +255,7 @@ const float before = best_v[mt];
 // a (j, j + d/2) pair, each computed as two features of one wave.  2 x 6 rows of the 256-wide configuration: 13 launches
 // and 110 us a layer before (3 + 2 projection launches, two norms, activation, rotation), see layer.hip for the rest.  A launch this
 // short also waits for its own instructions: with the row sums formed eight at a time (wave_sum8), 100 instructions fewer, q/k/v
-// takes 4.7 us instead of 7.1, gate / up 4.1 instead of 6.5, O and down 3.7 instead of 4.6.
+// takes 4.9 us instead of 7.1, gate / up 4.1 instead of 6.5, O and down 3.7 instead of 4.6.
 // ---------------------------------------------------------------------------
 constexpr int kF32Rows = 8;
 

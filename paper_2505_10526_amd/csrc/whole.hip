@@ -358,7 +358,12 @@ static int n_total(const GemmArgs& g) { return g.n[0] + g.n[1] + g.n[2]; }
 // q/k/v up to 48 rows, as 8 pairs a workgroup where that is one round of workgroups, else as 16.  us a layer, slabs and this:
 // 1.5B shape (128 workgroups of 8 pairs), 8 / 24 / 48 / 64 rows 48.3 -> 45.8, 52.2 -> 50.2, 60.1 -> 57.9, 67.1 -> 65.2; 7B (144 of 16),
 // 6 / 24 / 48 / 64 rows 107.7 -> 104.9, 115.0 -> 113.3, 124.6 -> 122.8, 150.7 -> 156.4 (8 pairs, 288 workgroups: 106.4, 115.4, 129.1 at
-// 6, 24, 48 rows); 12B (256 of 16), 24 / 48 / 64 rows 117.7 -> 112.5, 136.2 -> 131.2, 151.4 -> 155.3.
+// 6, 24, 48 rows); 12B (256 of 16), 24 / 48 / 64 rows 117.7 -> 112.5, 136.2 -> 131.2, 151.4 -> 155.3.  Few workgroups are no reason against it
+// either: 17 widths (hidden 256 to 5120, 16 to 224 workgroups), 1 to 48 rows, each of the three rules switched off against all on, a layer of
+// a stack: q/k/v 1.01 to 1.24 times as fast by this kernel, gate / up 0.99 to 1.07 (the shape with 10 tiles does not take it), O and down
+// 1.03 to 1.24 up to 8 rows, 1.00 to 1.08 at 17 to 32, and 0.98 to 1.25 at 9 to 16, where hidden 1152 to 2048 with an mlp of 7000 to 11000
+// (72 to 128 workgroups) gain nothing from it.  Against slabs throughout, no layer of 18 widths and 1 to 64 rows is slower beyond the
+// spread (0.99 to 1.48 times as fast).
 bool whole_qkv_pays(const GemmArgs& g) {
     return g.dtype == MASSV_BF16 && g.M <= 48 && n_total(g) / 32 <= kWholeGroups && gemm_supported(g) == MASSV_OK;
 }
