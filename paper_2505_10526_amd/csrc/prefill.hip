@@ -611,19 +611,21 @@ void prefill_attention_lds_kernel(PrefillParams p) {
 // The blocks travel through a ring of five (all 160 KB): a wave asks for one as it opens a pair and for the next between the
 // two blocks.  With a ring of two pairs and both asked for at once, a request held its wave as long as the memory took to accept it, and
 // all waves stood still together: caches of 1200 rows and more that are not in the last-level cache, tiles of 128 rows, were 3 to 9 %
-// slower than by 32 rows a wave (1 x 64 positions on 6000 211 us; ring of five, both at once 218).
+// slower than by 32 rows a wave (1 x 64 positions on 6000 211 us; ring of five, both at once 218, 32 rows a wave 197).
 // Key fragments lie as in the cache, 1 KB each.  Piece c (8 keys) of dim v lies at place c ^ (-(v / 4)) % 4 of the dim's four:
 // a fragment's 16 dims x 4 pieces then are free of bank conflicts (c ^ (v / 4) % 4, right for 32 dims x 2 pieces, cost two cycles
 // a read).  The even and odd steps of a score are chains of their own; their sum also keeps the maximum, which is
 // assembly, from reading a matrix result directly (the compiler does not wait for one there).
+// The places of the ring rotate through five registers: as blk % 5, or counted and wrapped, they were work on the path from the barrier
+// to the first keys (1 x 64 on 6000 184 us, 188 and now 174).
 // 16 / 8 heads, caches not in the last-level cache, us by 32 rows a wave, ring of two pairs and now, in turn on one card: second pieces
-// of 4 prompts of up to 1500 positions on up to 600 cached, window 1024, image block 149, 136 and 135; 4 x 2000 171, 159, 158; 8 x 1500
-// on 1000, window 1024 301, 274, 270; 1 x 2048 on 6000 267, 278, 256; 1 x 64 on 6000 197, 212, 184; 1 x 1000 39.8, 36.8, 36.3; 300 on
-// 1500 64.0, 60.8, 58.7; 100 rows 10.7, 9.3, 9.4; one row on 3000 cached ones 88, 73, 72, 16 of them 97, 99, 87.  Over 6600 calls (1 to
-// 4096 rows, caches to 8000, windows, in and out of the last-level cache) none is slower than by 32 rows a wave beyond 1.5 %.  Tried: two
-// waves that share 32 rows and exchange halves of the scores, a barrier a block (4 to 12 % slower than 32 rows a wave); four waves and
-// half the ring, two workgroups a compute unit (25 to 60 % slower); one load a thread that brings the pair after the next as far as L2
-// (up to 25 % slower); places of the ring counted instead of blk % 5 (2 % slower); all of a block's keys ahead (spills).
+// of 4 prompts of up to 1500 positions on up to 600 cached, window 1024, image block 149, 136 and 131; 4 x 2000 171, 159, 154; 8 x 1500
+// on 1000, window 1024 304, 274, 264; 1 x 2048 on 6000 268, 279, 250; 1 x 64 on 6000 197, 211, 174; 1 x 1000 39.8, 36.9, 35.3; 300 on
+// 1500 63.9, 61.0, 56.7; 100 rows 10.6, 9.3, 9.3; one row on 3000 cached ones 87, 73, 71, 16 of them 97, 98, 87.  Over 6600 calls (1 to
+// 4096 rows, caches to 8000, windows, in and out of the last-level cache) none is slower than by 32 rows a wave.  Tried: two waves that
+// share 32 rows and exchange halves of the scores, a barrier a block (4 to 12 % slower than 32 rows a wave); four waves and half the
+// ring, two workgroups a compute unit (25 to 60 % slower); one load a thread that brings the pair after the next as far as L2 (up to
+// 25 % slower); all of a block's keys ahead (spills).
 // ---------------------------------------------------------------------------
 constexpr int kPf16Waves = 8, kPf16Threads = kPf16Waves * kWave, kPf16Ring = 5;
 template <int D>
@@ -672,16 +674,16 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
         else
             dst[lane] = *reinterpret_cast<const bf16x8_any*>(src);
     };
-    auto slot = [&](int blk) { return (int)((unsigned)blk % kPf16Ring) * 2 * BP; };
-    auto request = [&](int blk) {
-        bf16x8* dst = pf_lds + slot(blk) + wave * kWave;
+    int ring[kPf16Ring] = {0, 2 * BP, 4 * BP, 6 * BP, 8 * BP};       // places of blocks blk0, blk0 + 1, ... in pf_lds
+    auto request = [&](int blk, int place) {
+        bf16x8* dst = pf_lds + place + wave * kWave;
 #pragma unroll
         for (int u = 0; u < NL; ++u) bring(kc + ((size_t)blk * BP + u * kPf16Threads) * 8, dst + u * kPf16Threads);
 #pragma unroll
         for (int u = 0; u < NL; ++u) bring(vc + ((size_t)blk * BP + u * kPf16Threads) * 8, dst + BP + u * kPf16Threads);
     };
-    request(blk_begin);
-    if (blk_begin + 1 < blk_end) request(blk_begin + 1);
+    request(blk_begin, ring[0]);
+    if (blk_begin + 1 < blk_end) request(blk_begin + 1, ring[1]);
 
     bf16x8 qreg[KS];
     int hi_row, lo_row;
@@ -704,7 +706,11 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
     for (int nt = 0; nt < NT; ++nt) acc[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
     constexpr float kLazy = 8.0f;                  // a row's reference exponent is raised only when exceeded by 2^8
 
-    for (int blk0 = blk_begin; blk0 < blk_end; blk0 += 2) {
+    auto turn = [&]() {
+        const int a = ring[0], b = ring[1];
+        ring[0] = ring[2]; ring[1] = ring[3]; ring[2] = ring[4]; ring[3] = a; ring[4] = b;
+    };
+    for (int blk0 = blk_begin; blk0 < blk_end; blk0 += 2, turn()) {
         // these two blocks have landed for every wave (a wave's requests complete in order; the block behind them may still be on
         // its way) and everybody is done with the two before, whose places take the next
         if constexpr (DIRECT) {
@@ -715,18 +721,18 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         const int first = blk0 > blk_first ? blk0 : blk_first, last = blk0 + 1 < blk_last ? blk0 + 1 : blk_last;
-        for (int blk = blk0 + (blk0 > blk_begin ? 3 : 2); blk <= blk0 + 3; ++blk)
-            if (blk < blk_end) request(blk);
-        if (first >= last && blk0 + 4 < blk_end) request(blk0 + 4);
+        if (blk0 == blk_begin && blk0 + 2 < blk_end) request(blk0 + 2, ring[2]);
+        if (blk0 + 3 < blk_end) request(blk0 + 3, ring[3]);
+        if (first >= last && blk0 + 4 < blk_end) request(blk0 + 4, ring[4]);
         if (first > last) continue;
         {
-            const bf16x8* kp = kfrag + slot(first);
+            const bf16x8* kp = kfrag + (first == blk0 ? ring[0] : ring[1]);
 #pragma unroll
             for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kp[ks * 64]; ka[ks][1] = kp[(KS + ks) * 64]; }
         }
         for (int blk = first; blk <= last; ++blk) {
-            const bf16x8* kp = kfrag + slot(blk);
-            const bf16x8* vp = vfrag + slot(blk);
+            const bf16x8* kp = kfrag + (blk == blk0 ? ring[0] : ring[1]);
+            const bf16x8* vp = vfrag + (blk == blk0 ? ring[0] : ring[1]);
             bf16x8 kb[KS / 2][2];
             floatx4 s[2][2];                       // [keys 8 lc + 4 t + (0..3)][even, odd steps] of row lr
 #pragma unroll
@@ -784,8 +790,8 @@ void prefill_attention_rows16_kernel(PrefillParams p) {
             l_run += ps;
             __builtin_amdgcn_s_setprio(0);
             if (blk < last) {
-                if (blk0 + 4 < blk_end) request(blk0 + 4);
-                const bf16x8* kn = kfrag + slot(blk + 1);
+                if (blk0 + 4 < blk_end) request(blk0 + 4, ring[4]);
+                const bf16x8* kn = kfrag + ring[1];
 #pragma unroll
                 for (int ks = 0; ks < KS / 2; ++ks) { ka[ks][0] = kn[ks * 64]; ka[ks][1] = kn[(KS + ks) * 64]; }
             }
