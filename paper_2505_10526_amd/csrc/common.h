@@ -58,6 +58,17 @@ __device__ inline float4 ldg_stream(const float4* p) {
     return make_float4(v[0], v[1], v[2], v[3]);
 }
 
+// ---- stores past the L2 ----
+// What a kernel leaves dirty in the dies' L2s (4 MB each) is written back when it ends, with nothing else going on, and while it runs a
+// stream of weights pushes it out in halves of lines.  Written through (agent scope), results go out as they come.  It pays where a launch that
+// reads far more than the caches hold leaves megabytes of results: see where it is used.  The wait state is for the registers of a
+// 16-byte store, which the compiler does not see to be one.
+template <typename V>
+__device__ inline void store_through(V* p, V v) {
+    static_assert(sizeof(V) == 16, "");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+}
+
 // ---- operand-order ("packed") activations ----
 // The bf16 projections read their activation matrix X[M][K] as the B operand
 // of v_mfma_f32_16x16x32_bf16: lane l of a wave needs the 8 values

@@ -61,6 +61,9 @@ __device__ inline float exp2_scaled(float d, float hi, float lo) {
 // 48 rows, 3584 -> 152064, whole calls: logits and accept at T > 0 250 -> 232 us, T = 0 196 -> 175, logits alone 202 ->
 // 197; 64 rows, 1536 wide, 197 -> 143 at T > 0).  Neighbouring workgroups hold neighbouring shares at any time: with a
 // workgroup's shares side by side instead the logits took 203 us.
+// What the shares' ends cost at 48 rows, 3584 -> 152064, T = 0.7 (whole call): logits stored into L2, which gives them back when the launch ends,
+// 230.9 us, written through 211.4 (non-temporal 211.1; not stored at all 200), and with the statistics' rare part (a new maximum)
+// behind a branch 205.0; 24 rows, 3840 -> 262144, 365 -> 340; T = 0, where nothing is stored, 182.1 -> 178.6 by the branch.
 // EPI_ARGMAX and EPI_LOGITS_STATS carry a lane's maximum (and sum) across the workgroup's shares: one record per row and
 // workgroup.
 // MANY: more than one share a workgroup (with the loop over shares compiled in, single ones took up to 9 % longer: 16 rows, 1024
@@ -134,6 +137,13 @@ void gemm_vocab_kernel(GemmDev g) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) { best_v[mt] = -INFINITY; best_i[mt] = INT_MAX; sum_e[mt] = 0.0; }
 
+    // Logits of more than 16 rows are written through L2 (store_through); fewer rows stay there for the accept rule, which reads them next (6 rows of
+    // 152064 191 us either way, one row 88.4 and 89.3 us a call).
+    auto put_logits = [&](int m, int col, floatx4 v) {
+        floatx4* dst = reinterpret_cast<floatx4*>((float*)g.y + (size_t)m * g.ldy + col);
+        if constexpr (MT > 1) store_through(dst, v);
+        else *dst = v;
+    };
     // Barrier for what travels through LDS; loads on their way into registers stay on their way.
     auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     int par = 0;
@@ -187,20 +197,23 @@ void gemm_vocab_kernel(GemmDev g) {
                     const int m = mt * 16 + lr;
                     const int col = (first + nt) * 16 + lc * 4;      // 4 consecutive output features
                     if (EPI == EPI_ARGMAX || STATS) {
-const float before = best_v[mt];
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)                   // ascending columns: a tie keeps the lower one
-                            if (s[i] > best_v[mt] || (s[i] == best_v[mt] && col + i < best_i[mt])) { best_v[mt] = s[i]; best_i[mt] = col + i; }
+                        // (a lane's columns ascend: a tie keeps the lower one; a row of -inf alone gets its first column)
+                        const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+                        if (mx > best_v[mt] || (mx == best_v[mt] && best_i[mt] == INT_MAX)) {
+                            if constexpr (STATS)
+                                if (mx > best_v[mt]) sum_e[mt] *= (double)exp2_scaled(best_v[mt] - mx, g.ts_hi, g.ts_lo);
+                            best_v[mt] = mx;
+                            best_i[mt] = col + (s[0] == mx ? 0 : s[1] == mx ? 1 : s[2] == mx ? 2 : 3);
+                        }
                         if constexpr (STATS) {
                             float four = 0.f;
 #pragma unroll
                             for (int i = 0; i < 4; ++i) four += exp2_scaled(s[i] - best_v[mt], g.ts_hi, g.ts_lo);
-                            if (best_v[mt] > before) sum_e[mt] *= (double)exp2_scaled(before - best_v[mt], g.ts_hi, g.ts_lo);
                             sum_e[mt] += (double)four;
                         }
-                        if (STATS && m < g.M) *reinterpret_cast<floatx4*>((float*)g.y + (size_t)m * g.ldy + col) = s;
+                        if (STATS && m < g.M) put_logits(m, col, s);
                     } else if (m < g.M) {
-                        *reinterpret_cast<floatx4*>((float*)g.y + (size_t)m * g.ldy + col) = s;
+                        put_logits(m, col, s);
                     }
                 }
             }

@@ -507,6 +507,27 @@ def test_vocabulary_statistics_carried_across_shares_keep_small_terms():
     assert torch.equal(logits[0], w[:, 0].float())
 
 
+@pytest.mark.parametrize("rising", [False, True], ids=["equal", "rising"])
+@pytest.mark.parametrize("M", [5, 16, 17, 48, 64])
+def test_vocabulary_maximum_that_never_and_always_moves(M, rising):
+    """Statistics of rows whose logits are all equal (the first column holds the maximum from the start) and of rows that rise with the
+    column (every piece of every share brings a new maximum), at one to four row tiles and three shares a workgroup: the greedy
+    token, and at T = 1 the same integers as from the logits themselves."""
+    H, V = 64, 81328
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    x = torch.rand(M, H, generator=g, device="cuda").to(torch.bfloat16) + 0.25            # positive: a row's logits follow the weights
+    w = (torch.arange(V, device="cuda") * (16.0 / V) if rising else torch.ones(V, device="cuda"))[:, None].expand(V, H).to(torch.bfloat16).contiguous()
+    wp = binding.weight_pack(w)
+    n, tok = binding.lm_head_greedy_accept(x.view(M, 1, H), None, wp, None)
+    logits = binding.lm_head_logits(x, None, wp)
+    assert torch.equal(tok.view(-1).long(), logits.argmax(-1)) and (rising or not tok.any())
+    u = torch.rand(M, 1, generator=g, device="cuda") * 0.999
+    n1, t1, l1 = binding.lm_head_accept(x.view(M, 1, H), None, wp, None, None, u, 1.0)
+    n2, t2 = binding.spec_accept(logits.view(M, 1, V), None, None, u, 1.0)
+    assert torch.equal(l1.view(M, V), logits) and torch.equal(n1, n2) and torch.equal(t1, t2)
+
+
 @pytest.mark.parametrize("H", [7, 64, 68, 252, 256, 260, 512, 700, 1028])
 @pytest.mark.parametrize("M,V", [(1, 100), (2, 4097), (3, 33), (4, 5000), (5, 70), (8, 4096), (9, 4100), (17, 64)])
 def test_fp32_logits_rows_and_widths(M, V, H):
