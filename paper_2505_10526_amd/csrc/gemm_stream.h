@@ -200,7 +200,8 @@ void gemm_stream_kernel(typename GemmDevOf<EPI>::type g) {
                     }
                 } else if (m < g.M) {
                     float* dst = (float*)g.y + (size_t)by * g.slab_stride + (size_t)m * g.ldy + col;
-                    *reinterpret_cast<floatx4*>(dst) = s;
+                    if constexpr (MT > 1) store_through(reinterpret_cast<floatx4*>(dst), s);
+                    else *reinterpret_cast<floatx4*>(dst) = s;
                 }
             }
         }
