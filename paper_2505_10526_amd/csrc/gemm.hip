@@ -505,7 +505,7 @@ int gemm_supported(const GemmArgs& g) {
 //   weights at 6.5 TB/s, stretched when fewer than 256 workgroups pull them;
 //   X, re-read from L2 once per workgroup column: (T / nt) * K/32 * MT KB, at 14 TB/s;
 //   0.8 us per MB of partial sums (written here, read back by the next kernel).  Of more than 16 rows they are written through L2
-//   (store_through): 48-row layer 128.2 -> 126.0 us, 24-row 12B layer 121.2 -> 120.7; of 6 and 10 rows 100.1 and 110.5 us cached,
+//   (store_through): 48-row layer 126.0 -> 125.3 us (128.2 -> 126.0 on another card), 28 rows of a drafter 1538 -> 1528; of 6 and 10 rows 100.1 and 110.5 us cached,
 //   100.2 and 110.9 through.
 // Measured against the earlier rule "as many slabs as fill 256 workgroups, largest tile count": q/k/v (8 tiles, 7
 // slabs) -> (4, 3) -1.9 us, output projection (7, 7) -> (4, 4) -1.0 us, down projection (7, 8) unchanged.
