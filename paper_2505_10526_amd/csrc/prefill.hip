@@ -361,19 +361,26 @@ void prefill_attention_kernel(PrefillParams p) {
 // fragment are 64 bytes apart, which as they lie in the cache is four lanes to a bank.
 // Waves without rows only bring their share of the blocks in (multiplying the last row along made calls of up to 32
 // rows 4 to 12 % slower).
+// HALVES = 2: a second group of four waves takes the later half of the key blocks, through a ring of its own, and the two sums are put together in
+// LDS at the end.  What bounds these launches is the length of one wave's chain of blocks, with nothing else on its SIMD: now it is
+// half as long and every SIMD has two.  All in vector registers (211 at d = 128; with the sums in accumulation registers, 128 and
+// 126, the moves between them ate the gain: 1000 rows on 6000 93 us).  28 / 4 heads of 128, one half and two: 1 x 1111 rows 30.3 and 26.9 us,
+// 1 x 800 24.2 and 21.2, 1000 on 6000 108.4 and 85.8, 16 on 8000 133.7 and 101.9; 14 / 2 heads of 64, 1 x 1111 22.1 and 17.2, 1000 on 6000
+// 79.7 and 52.9.  Under kPfCutBlocks blocks the first group does it alone (200 rows, 7 blocks: 10.0 us, cut 11.8).
 // ---------------------------------------------------------------------------
 constexpr int kPfRing = 4;
+constexpr int kPfCutBlocks = 10;
 constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 64 KB at d = 128
 
-template <int D, bool DIRECT>
-__global__ __launch_bounds__(kPfThreads)
+template <int D, bool DIRECT, int HALVES>
+__global__ __launch_bounds__(kPfThreads * HALVES)
 void prefill_attention_lds_kernel(PrefillParams p) {
     constexpr int KS = D / 16, NT = D / 32, BP = D * 4;      // BP: 16-byte pieces of a block's keys (or values)
     constexpr int NL = BP / kPfThreads;                               // requests a lane makes for a block's keys (and values)
     const int pair = blockIdx.x, b = pair / p.n_kv, g = pair % p.n_kv;
     const int tile = p.n_tiles - 1 - (int)blockIdx.y;                 // the longest key ranges are started first
-    const int tid = threadIdx.x, lane = tid % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int tid = threadIdx.x % kPfThreads, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), half = HALVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kPfThreads);
     const int lr = lane % 32, hh = lane / 32;
     const int G = p.n_q / p.n_kv;
     const int L = cached_rows(p.kv_len[b], p.l_max);
@@ -392,12 +399,21 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     auto pos_of = [&](int r) { return (r < rows ? r : rows - 1) / G; };
     const int min_hi = pf_hi(L + pos_of(r0), m_bidir, total), max_hi = pf_hi(L + pos_of(r0 + 31), m_bidir, total);
     const int min_lo = pf_lo(L + pos_of(r0), W), max_lo = pf_lo(L + pos_of(r0 + 31), W);
-    const int blk_first = min_lo / kPfBlk, blk_last = (max_hi - 1) / kPfBlk;          // blocks of this wave
-    // blocks of the workgroup (visibility moves up with the row)
-    const int blk_begin = pf_lo(L + pos_of(w0), W) / kPfBlk;
-    const int blk_end = (pf_hi(L + pos_of(w0 + kPfWaves * 32 - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
+    // blocks of the workgroup (visibility moves up with the row), of this half of it (few are not worth a second one), and of this wave
+    const int all_begin = pf_lo(L + pos_of(w0), W) / kPfBlk;
+    const int all_end = (pf_hi(L + pos_of(w0 + kPfWaves * 32 - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
+    const int cut = HALVES == 1 || all_end - all_begin < kPfCutBlocks ? all_end : (all_begin + all_end + 1) / 2;
+    const int blk_begin = half ? cut : all_begin, blk_end = half ? all_end : cut;
+    int blk_first = min_lo / kPfBlk, blk_last = (max_hi - 1) / kPfBlk;
+    const bool whole = HALVES == 1 || cut == all_end;
+    if (HALVES == 2) {
+        if (half && whole) return;                                    // (a barrier waits for the waves that are still there)
+        blk_first = blk_first > blk_begin ? blk_first : blk_begin;
+        blk_last = blk_last < blk_end - 1 ? blk_last : blk_end - 1;
+    }
 
-    extern __shared__ bf16x8 pf_lds[];                                // [kPfRing][keys | values][BP]
+    extern __shared__ bf16x8 pf_lds_all[];                            // [HALVES][kPfRing][keys | values][BP]
+    bf16x8* const pf_lds = pf_lds_all + half * (kPfRing * 2 * BP);
     // DIRECT: caches that start at a multiple of 16 bytes.  Others travel through registers (a load to LDS takes 16 bytes
     // from a multiple of 16 only; an ordinary load takes them from anywhere).
     const bf16_t* const kc = p.kc + bg * (size_t)p.l_max * D + tid * 8;
@@ -443,147 +459,186 @@ void prefill_attention_lds_kernel(PrefillParams p) {
         if (blk_begin + 1 < blk_end) request(blk_begin + 1);
         if (blk_begin + 2 < blk_end) request(blk_begin + 2);
     };
+    const bool idle = r0 >= rows || blk_first > blk_last;     // such a wave only brings its share of the blocks in
     request_first();
-    if (r0 >= rows) {                              // a wave past the last row only brings its share of the blocks in
+    if (idle) {
         start();
         for (int blk = blk_begin; blk < blk_end; ++blk) open(blk);
-        return;
     }
+    if (idle && whole) return;
 
-    bf16x8 qreg[KS];
-    int hi_row, lo_row;
-    {
-        const int r = r0 + lr < rows ? r0 + lr : rows - 1;
-        const int i = r / G, qh = r % G;
-        hi_row = pf_hi(L + i, m_bidir, total);
-        lo_row = pf_lo(L + i, W);
-        const bf16_t* qr = p.q + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 16 + hh * 8);
-    }
-
-    // fragments: key slot lr of a block lies in half (lr / 8) % 2 at place 4 (2 (lr / 16) + (lr / 4) % 2) + lr % 4
-    const bf16x8* const kfrag = pf_lds + ((lr / 8) % 2) * (BP / 2) + hh * 16 + 4 * (2 * (lr / 16) + (lr / 4) % 2) + lr % 4;
-    const bf16x8* const vfrag = pf_lds + BP + lr * 4;
-    const int vx = (lr / 4) % 4;
-    bf16x8 k0[KS], v0[NT][2];
-    auto load_k = [&](int blk) {
-        const bf16x8* kp = kfrag + (blk % kPfRing) * 2 * BP;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) k0[ks] = kp[ks * 32];
-    };
-    auto load_v = [&](int blk) {
-        const bf16x8* vp = vfrag + (blk % kPfRing) * 2 * BP;
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) v0[nt][t] = vp[nt * 128 + ((2 * t + hh) ^ vx)];
-    };
-
-    floatx16 acc[NT], sc, sn, so;
+    floatx16 acc[NT];
     float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[nt][e] = 0.f;
-    bf16x8 pv[2];
-    auto chains = [&]() {                          // S^T of the block whose keys k0 holds: even k-steps in sn, odd in so
-        const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (!idle) {
+        bf16x8 qreg[KS];
+        int hi_row, lo_row;
+        {
+            const int r = r0 + lr < rows ? r0 + lr : rows - 1;
+            const int i = r / G, qh = r % G;
+            hi_row = pf_hi(L + i, m_bidir, total);
+            lo_row = pf_lo(L + i, W);
+            const bf16_t* qr = p.q + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D;
 #pragma unroll
-        for (int ks = 0; ks < KS; ks += 2) {
-            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[ks], qreg[ks], ks == 0 ? zero : sn, 0, 0, 0);
-            so = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[ks + 1], qreg[ks + 1], ks == 0 ? zero : so, 0, 0, 0);
+            for (int ks = 0; ks < KS; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8*>(qr + ks * 16 + hh * 8);
         }
-    };
-    constexpr float kLazy = 8.0f;                  // a row's reference exponent is raised only when exceeded by 2^8
-    auto soft_max = [&](int blk) {                 // value v of the lane is key key0 + 16 (v / 8) + v % 8
-        const int key0 = blk * kPfBlk + hh * 8;
-        if ((blk + 1) * kPfBlk > min_hi || blk * kPfBlk < max_lo) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int key = key0 + 16 * (v / 8) + v % 8;
-                if (key >= hi_row || key < lo_row) sc[v] = -INFINITY;
-            }
-        }
-        float mx = pf_max3(pf_max3(pf_max3(sc[0], sc[1], sc[2]), pf_max3(sc[3], sc[4], sc[5]), pf_max3(sc[6], sc[7], sc[8])),
-                           pf_max3(pf_max3(sc[9], sc[10], sc[11]), pf_max3(sc[12], sc[13], sc[14]), sc[15]), sc[15]);
-        mx *= p.scale_log2;
-        if (__any(mx > m_run + kLazy)) {
-            mx = pf_xor32_max(mx);
-            if (mx > m_run + kLazy) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - mx);     // m_run = -inf gives 0
-                l_run *= alpha;
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    // keeps the copies out of the accumulation registers inside this rare branch
-                    asm volatile("" : "+a"(acc[nt]));
-                    acc[nt] *= alpha;
-                }
-                m_run = mx;
-            }
-        }
-    };
-    auto soft_exp = [&](float neg_m) {
-        float ps = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float pe = __builtin_amdgcn_exp2f(fmaf(sc[v], p.scale_log2, neg_m));
-            ps += pe;
-            pv[v / 8][v % 8] = (bf16_t)pe;
-        }
-        return ps;
-    };
-    auto product = [&]() {                         // O^T += V^T P^T
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0[nt][t], pv[t], acc[nt], 0, 0, 0);
-    };
 
-    start();
-    int blk = blk_begin;
-    for (; blk < blk_first; ++blk) open(blk);      // blocks that only the rows of other waves see
-    load_k(blk);
-    chains();
-    sc = sn + so;
-    for (; blk < blk_last; ++blk) {
-        open(blk);
-        load_k(blk + 1);
-        load_v(blk);
-        soft_max(blk);
-        const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-        __builtin_amdgcn_sched_barrier(0);
-        chains();
-        float ps = soft_exp(neg_m);
+        // fragments: key slot lr of a block lies in half (lr / 8) % 2 at place 4 (2 (lr / 16) + (lr / 4) % 2) + lr % 4
+        const bf16x8* const kfrag = pf_lds + ((lr / 8) % 2) * (BP / 2) + hh * 16 + 4 * (2 * (lr / 16) + (lr / 4) % 2) + lr % 4;
+        const bf16x8* const vfrag = pf_lds + BP + lr * 4;
+        const int vx = (lr / 4) % 4;
+        bf16x8 k0[KS], v0[NT][2];
+        auto load_k = [&](int blk) {
+            const bf16x8* kp = kfrag + (blk % kPfRing) * 2 * BP;
 #pragma unroll
-        for (int m = 0; m < KS; ++m) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 32 / KS, 0);
-            __builtin_amdgcn_sched_group_barrier(0x400, 16 / KS, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 32 / KS, 0);
-        }
-        // (without a use here the compiler moves the exponentials down to the second product, their first use)
-        asm volatile("" : "+v"(pv[0]), "+v"(pv[1]), "+v"(ps));
-        __builtin_amdgcn_sched_barrier(0);
-        l_run += ps;
-        product();
-        sc = sn + so;
-    }
-    open(blk);
-    load_v(blk);
-    if ((blk + 1) * kPfBlk > total) {              // values of rows past the valid ones may hold anything
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+            for (int ks = 0; ks < KS; ++ks) k0[ks] = kp[ks * 32];
+        };
+        auto load_v = [&](int blk) {
+            const bf16x8* vp = vfrag + (blk % kPfRing) * 2 * BP;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (blk * kPfBlk + hh * 8 + 16 * t + e >= total) v0[nt][t][e] = (bf16_t)0.f;
+                for (int nt = 0; nt < NT; ++nt) v0[nt][t] = vp[nt * 128 + ((2 * t + hh) ^ vx)];
+        };
+
+        floatx16 sc, sn, so;
+        bf16x8 pv[2];
+        auto chains = [&]() {                          // S^T of the block whose keys k0 holds: even k-steps in sn, odd in so
+            const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ks += 2) {
+                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[ks], qreg[ks], ks == 0 ? zero : sn, 0, 0, 0);
+                so = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[ks + 1], qreg[ks + 1], ks == 0 ? zero : so, 0, 0, 0);
+            }
+        };
+        constexpr float kLazy = 8.0f;                  // a row's reference exponent is raised only when exceeded by 2^8
+        auto soft_max = [&](int blk) {                 // value v of the lane is key key0 + 16 (v / 8) + v % 8
+            const int key0 = blk * kPfBlk + hh * 8;
+            if ((blk + 1) * kPfBlk > min_hi || blk * kPfBlk < max_lo) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int key = key0 + 16 * (v / 8) + v % 8;
+                    if (key >= hi_row || key < lo_row) sc[v] = -INFINITY;
+                }
+            }
+            float mx = pf_max3(pf_max3(pf_max3(sc[0], sc[1], sc[2]), pf_max3(sc[3], sc[4], sc[5]), pf_max3(sc[6], sc[7], sc[8])),
+                               pf_max3(pf_max3(sc[9], sc[10], sc[11]), pf_max3(sc[12], sc[13], sc[14]), sc[15]), sc[15]);
+            mx *= p.scale_log2;
+            if (__any(mx > m_run + kLazy)) {
+                mx = pf_xor32_max(mx);
+                if (mx > m_run + kLazy) {
+                    const float alpha = __builtin_amdgcn_exp2f(m_run - mx);     // m_run = -inf gives 0
+                    l_run *= alpha;
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        // keeps the copies out of the accumulation registers inside this rare branch
+                        if constexpr (HALVES == 1) asm volatile("" : "+a"(acc[nt]));
+                        else asm volatile("" : "+v"(acc[nt]));
+                        acc[nt] *= alpha;
+                    }
+                    m_run = mx;
+                }
+            }
+        };
+        auto soft_exp = [&](float neg_m) {
+            float ps = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float pe = __builtin_amdgcn_exp2f(fmaf(sc[v], p.scale_log2, neg_m));
+                ps += pe;
+                pv[v / 8][v % 8] = (bf16_t)pe;
+            }
+            return ps;
+        };
+        auto product = [&]() {                         // O^T += V^T P^T
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0[nt][t], pv[t], acc[nt], 0, 0, 0);
+        };
+
+        start();
+        int blk = blk_begin;
+        for (; blk < blk_first; ++blk) open(blk);      // blocks that only the rows of other waves see
+        load_k(blk);
+        chains();
+        sc = sn + so;
+        for (; blk < blk_last; ++blk) {
+            open(blk);
+            load_k(blk + 1);
+            load_v(blk);
+            soft_max(blk);
+            const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+            __builtin_amdgcn_sched_barrier(0);
+            chains();
+            float ps = soft_exp(neg_m);
+#pragma unroll
+            for (int m = 0; m < KS; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 32 / KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x400, 16 / KS, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 32 / KS, 0);
+            }
+            // (without a use here the compiler moves the exponentials down to the second product, their first use)
+            asm volatile("" : "+v"(pv[0]), "+v"(pv[1]), "+v"(ps));
+            __builtin_amdgcn_sched_barrier(0);
+            l_run += ps;
+            product();
+            sc = sn + so;
+        }
+        open(blk);
+        load_v(blk);
+        if ((blk + 1) * kPfBlk > total) {              // values of rows past the valid ones may hold anything
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (blk * kPfBlk + hh * 8 + 16 * t + e >= total) v0[nt][t][e] = (bf16_t)0.f;
+        }
+        soft_max(blk);
+        l_run += soft_exp((m_run == -INFINITY) ? 0.f : -m_run);
+        product();
+        for (++blk; blk < blk_end; ++blk) open(blk);
     }
-    soft_max(blk);
-    l_run += soft_exp((m_run == -INFINITY) ? 0.f : -m_run);
-    product();
-    for (++blk; blk < blk_end; ++blk) open(blk);
+
+    // The halves' sums: each wave hands its partner the dims that the partner finishes and takes those of its own.
+    if (!whole) {
+        constexpr int NH = NT / 2;
+        if (all_end - cut < cut - all_begin && half) barrier();       // (one a block: as many in either half)
+        floatx4* const mine = reinterpret_cast<floatx4*>(pf_lds_all) + (half * kPfWaves + wave) * (NH * 4 + 1) * kWave + lane;
+        const floatx4* const other = reinterpret_cast<const floatx4*>(pf_lds_all) + ((1 - half) * kPfWaves + wave) * (NH * 4 + 1) * kWave + lane;
+        __syncthreads();
+#pragma unroll
+        for (int nt = 0; nt < NH; ++nt)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const floatx16& v = half ? acc[nt] : acc[NH + nt];
+                mine[(nt * 4 + q4) * kWave] = floatx4{v[4 * q4], v[4 * q4 + 1], v[4 * q4 + 2], v[4 * q4 + 3]};
+            }
+        mine[NH * 4 * kWave] = floatx4{m_run, l_run, 0.f, 0.f};
+        __syncthreads();
+        const floatx4 ml = other[NH * 4 * kWave];
+        const float m = fmaxf(m_run, ml[0]);
+        const float a = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m), c = ml[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[0] - m);
+        l_run = l_run * a + ml[1] * c;
+#pragma unroll
+        for (int nt = 0; nt < NH; ++nt)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const floatx4 o = other[(nt * 4 + q4) * kWave];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float x = half ? acc[NH + nt][4 * q4 + e] : acc[nt][4 * q4 + e];
+                    acc[nt][4 * q4 + e] = x * a + o[e] * c;
+                }
+            }
+        if (r0 >= rows) return;
+    }
 
     // ---- write this wave's rows: lane holds dims 32 nt + 8 (v / 4) + 4 hh + v % 4 of row lr ----
     const float l = l_run + __shfl_xor(l_run, 32, kWave);
@@ -591,15 +646,17 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     if (r >= rows) return;
     const float inv = 1.0f / l;                    // every row sees at least its own key
     const int i = r / G, qh = r % G;
-    bf16_t* dst = p.out + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D + hh * 4;
+    bf16_t* dst = p.out + (((size_t)b * p.Lq + i) * p.n_q + g * G + qh) * D + half * (D / 2) + hh * 4;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT; ++nt) {
+        if (HALVES == 2 && nt >= NT / 2 && !whole) break;
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const floatx16& v = acc[nt];
             bf16x4 o = {(bf16_t)(v[4 * q4] * inv), (bf16_t)(v[4 * q4 + 1] * inv), (bf16_t)(v[4 * q4 + 2] * inv), (bf16_t)(v[4 * q4 + 3] * inv)};
             *reinterpret_cast<bf16x4*>(dst + nt * 32 + q4 * 8) = o;
         }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -889,29 +946,31 @@ static int launch_prefill(const massv_attn_desc& a, PrefillParams p, hipStream_t
     return launch_status();
 }
 
-template <int D, bool DIRECT>
+template <int D, bool DIRECT, int HALVES>
 static int launch_prefill_lds(const massv_attn_desc& a, PrefillParams p, hipStream_t st) {
     // more LDS than a kernel gets by default: the limit is raised once per device
     static std::atomic<bool> ready[64];           // zero-initialised; calls may come from several threads
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MASSV_ELAUNCH;
     if (!ready[dev].load(std::memory_order_acquire)) {
-        if (hipFuncSetAttribute((const void*)prefill_attention_lds_kernel<D, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)pf_lds_bytes(D)) != hipSuccess) return MASSV_ELAUNCH;
+        if (hipFuncSetAttribute((const void*)prefill_attention_lds_kernel<D, DIRECT, HALVES>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                HALVES * (int)pf_lds_bytes(D)) != hipSuccess) return MASSV_ELAUNCH;
         ready[dev].store(true, std::memory_order_release);
     }
     const int rows_max = a.n_query * (a.n_q_heads / a.n_kv_heads);
     const int per_wg = kPfWaves * 32;
     p.n_tiles = (rows_max + per_wg - 1) / per_wg;
     if (p.n_tiles > 65535) return MASSV_EUNSUPPORTED;
-    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_lds_kernel<D, DIRECT>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
-                  dim3(kPfThreads), pf_lds_bytes(D), st, p);
+    launch_traced(MASSV_K_PREFILL_ATTENTION, prefill_attention_lds_kernel<D, DIRECT, HALVES>, dim3(a.batch * a.n_kv_heads, p.n_tiles),
+                  dim3(kPfThreads * HALVES), HALVES * pf_lds_bytes(D), st, p);
     return launch_status();
 }
 template <int D>
-static int launch_prefill_lds(const massv_attn_desc& a, const PrefillParams& p, hipStream_t st) {
+static int launch_prefill_lds(const massv_attn_desc& a, const PrefillParams& p, bool halves, hipStream_t st) {
     const bool direct = ((uintptr_t)p.kc | (uintptr_t)p.vc) % 16 == 0;
-    return direct ? launch_prefill_lds<D, true>(a, p, st) : launch_prefill_lds<D, false>(a, p, st);
+    if (D == 128 || halves) return direct ? launch_prefill_lds<D, true, 2>(a, p, st) : launch_prefill_lds<D, false, 2>(a, p, st);
+    if constexpr (D == 64) return direct ? launch_prefill_lds<D, true, 1>(a, p, st) : launch_prefill_lds<D, false, 1>(a, p, st);
+    return MASSV_EUNSUPPORTED;
 }
 
 template <int D, bool DIRECT>
@@ -971,22 +1030,25 @@ extern "C" int massv_prefill_attention(const massv_attn_desc* desc, const void* 
     p.Lq = a.n_query; p.n_q = a.n_q_heads; p.n_kv = a.n_kv_heads; p.l_max = a.l_max; p.window = a.window;
     p.n_tiles = 0;
     p.scale_log2 = scale * 1.4426950408889634f;
-    // d <= 128: a launch of 32 rows per wave that fits the chip (256 workgroups of 128 rows) is the faster one, by 1.16 to
-    // 1.65 over 300 calls: the length of one wave's loop counts there.  Larger ones take 64 rows per wave, with two exceptions.
-    // At d = 64 the smaller kernel stays ahead (1.05 to 1.5; its blocks are half as long) while workgroups of 256 rows would
+    // d <= 128: a launch of 32 rows per wave that fits the chip (256 workgroups of 128 rows, their key ranges in two halves) is the faster one,
+    // by 1.0 to 1.6: the length of one wave's loop counts there.  Larger ones take 64 rows per wave, with two exceptions.
+    // At d = 64 the smaller kernel, in one piece, stays ahead (1.05 to 1.5; its blocks are half as long) while workgroups of 256 rows would
     // fit the chip, unless a window makes them all alike (0.96 to 1.3) or rows are few before a long cache (100 rows on
-    // 6000: 0.95).  At d = 128 it does so for long fresh prompts alone (24 tiles of 128 rows a pair and more, 224 workgroups
-    // of 256 in all; 1 x 2000, 28 / 4 heads: 64 and 51 us), whose many short key ranges fill up what the long ones leave:
-    // with a cache as long as the prompt 110 and 119 us, with window 512 30.5 and 43.
+    // 6000: 0.95).  At d = 128 it does so, in halves, for fresh prompts of up to 512 workgroups, whose many short key ranges fill up
+    // what the long ones leave (64 rows a wave and halves: 28 / 4 heads, 4 x 300 20.0 and 14.8 us, 1 x 1500 39.6 and 34.1, 2 x 1000 32.3 and
+    // 30.9, 544 workgroups 22.6 and 24.2; 16 / 8 heads, 2 x 2000 61.4 and 47.9, 752 workgroups 89.0 and 95.5; with a cache as long as the
+    // prompt or longer 47.2 and 48.9, 62.8 and 70.3).
     const int64_t pairs = (int64_t)a.batch * a.n_kv_heads, rows = (int64_t)a.n_query * (a.n_q_heads / a.n_kv_heads);
     const int64_t wide = pairs * ((rows + kPfWaves * 64 - 1) / (kPfWaves * 64)), tiles = (rows + kPfWaves * 32 - 1) / (kPfWaves * 32);
     const bool banded = a.window > 0 && a.window < a.l_max;
-    bool few = pairs * tiles <= 256;
-    if (a.head_dim == 64) few = few || (!banded && wide <= 256 && a.l_max / 8 <= a.n_query);
-    else few = few || (!banded && !n_bidir && wide <= 224 && tiles >= 24 && (int64_t)a.l_max * 4 <= (int64_t)a.n_query * 5 + 128);
+    bool halves = pairs * tiles <= 256;
+    if (a.head_dim == 128)
+        halves = halves || (!banded && !n_bidir && pairs * tiles <= 512 && (a.n_query >= 256 || tiles >= 24) &&
+                             (int64_t)a.l_max * 4 <= (int64_t)a.n_query * 5 + 128);
+    const bool few = halves || (a.head_dim == 64 && !banded && wide <= 256 && a.l_max / 8 <= a.n_query);
     switch (a.head_dim) {
-        case 64: return few ? launch_prefill_lds<64>(a, p, st) : launch_prefill<64>(a, p, st);
-        case 128: return few ? launch_prefill_lds<128>(a, p, st) : launch_prefill<128>(a, p, st);
+        case 64: return few ? launch_prefill_lds<64>(a, p, halves, st) : launch_prefill<64>(a, p, st);
+        case 128: return few ? launch_prefill_lds<128>(a, p, halves, st) : launch_prefill<128>(a, p, st);
         case 256: return launch_prefill16<256>(a, p, st);
     }
     return MASSV_EUNSUPPORTED;

@@ -136,6 +136,18 @@ def test_rows_and_blocks_through_lds(heads, kv_len, n_new, window, bidir, d):
     run_case(s, kv_len, n_new, [t // 2 for t in total], seed=sum(total), window=window, bidir=bidir)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kv_len,n_new,window,bidir", [
+    ([270, 300, 310], [18, 20, 40], 0, False),          # 9, 10 and 11 blocks of keys: in one piece, in equal halves and in halves that differ by one
+    ([640, 400, 0], [70, 3, 33], 0, False),             # two workgroups of a pair, waves without rows, one without keys to cut
+    ([700, 420, 352], [64, 65, 1], 330, False),         # windows that open inside the first half
+    ([0, 40, 0], [400, 350, 321], 0, True)])            # an image block that sees itself across the cut
+def test_keys_in_two_halves(kv_len, n_new, window, bidir, d):
+    """Launches that fit the chip: the later half of a workgroup's key blocks belongs to a second group of waves."""
+    s = synth.LayerShape(512, 4, 2, d, 704, 4096, dtype="bf16")
+    run_case(s, kv_len, n_new, [min(300, n) for n in n_new], seed=d + n_new[0], window=window, bidir=bidir)
+
+
 @pytest.mark.parametrize("n_new", [7, 8, 9, 63, 64, 65])
 @pytest.mark.parametrize("kv_len,window", [(0, 0), (25, 0), (57, 0), (120, 40), (150, 40)])
 def test_row_tiles_and_block_pairs_d256(n_new, kv_len, window):
