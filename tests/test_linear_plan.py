@@ -1,0 +1,78 @@
+"""How massv_linear cuts a call into workgroups (csrc/linear_plan.h, plain host code, compiled here by itself): a call uses
+what massv_linear_workspace asks for and no more."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2505_10526_amd import binding
+
+CSRC = os.path.join(os.path.dirname(binding.__file__), "csrc")
+DRIVER = r"""
+#include "linear_plan.h"
+#include <cstdio>
+#include <cstring>
+#include <initializer_list>
+using namespace massv;
+static bool same(const LinPlan& a, const LinPlan& b) { return !memcmp(&a, &b, sizeof a); }
+// "plan M N K": the plan with the room asked for, and those bytes.  "rooms M0 M1 N K": over these row counts, the first where the plan with the room
+// asked for is not the plan with more, or where a smaller room does not hold what is planned into it (or 0), and how many split K.
+int main() {
+    char what[16];
+    int a, b, c, d;
+    while (scanf("%15s", what) == 1) {
+        if (!strcmp(what, "plan") && scanf("%d %d %d", &a, &b, &c) == 3) {
+            const LinPlan p = linear_plan(a, b, c, linear_asked_room(a, b, c));
+            printf("%d %d %d %zu\n", p.fj, p.parts, p.big, linear_asked_room(a, b, c));
+        } else if (!strcmp(what, "rooms") && scanf("%d %d %d %d", &a, &b, &c, &d) == 4) {
+            int bad = 0, split = 0;
+            for (int M = a; M <= b; ++M) {
+                const size_t asked = linear_asked_room(M, c, d), one = (size_t)M * c * 4;
+                const LinPlan all = linear_plan(M, c, d, asked);
+                split += all.parts > 1;
+                bool ok = linear_plan(M, c, d, 0).parts == 1 && linear_part_bytes(all, M, c) <= asked;
+                for (size_t more : {(size_t)0, one, 2 * one, (size_t)64 << 20, (size_t)1 << 33, kLinAnyRoom - asked}) ok = ok && same(linear_plan(M, c, d, asked + more), all);
+                for (size_t room = one; room < asked; room += one) ok = ok && linear_part_bytes(linear_plan(M, c, d, room + 255), M, c) <= room + 255;
+                if (!ok && !bad) bad = M;
+            }
+            printf("%d %d\n", bad, split);
+        } else return 1;
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("clang++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(DRIVER)
+    subprocess.check_call([cxx, "-O2", "-std=c++17", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan")])
+
+    def run(lines):
+        out = subprocess.run([str(d / "plan")], input="\n".join(lines), text=True, capture_output=True, check=True).stdout
+        return [tuple(int(v) for v in line.split()) for line in out.splitlines()]
+    return run
+
+
+# N, K of the maps of the 7B, 12B and 1.5B shapes and their projectors, and a few beside them
+WIDTHS = [(3584, 18944), (18944, 3584), (3584, 3584), (4608, 3584), (3840, 15360), (15360, 3840), (8192, 3840), (3840, 4096), (3840, 8192), (1536, 8960),
+          (8960, 1536), (2048, 1536), (1536, 1536), (5120, 5120), (3584, 5120), (5120, 1280), (4096, 10752), (4096, 11008), (11008, 4096), (320, 18944),
+          (512, 4160), (1024, 1024), (16, 64), (8192, 8192)]
+
+
+def test_more_room_than_asked_for_changes_nothing(ask):
+    got = ask([f"rooms 1 8000 {n} {k}" for n, k in WIDTHS])
+    assert [w for w, (bad, _) in zip(WIDTHS, got) if bad] == [], got
+    assert sum(split for _, split in got) > 5000                     # (plans that split K are what it is about)
+
+
+def test_the_library_asks_for_that_room(ask):
+    shapes = [(m, n, k) for n, k in WIDTHS for m in (1, 16, 60, 129, 150, 192, 300, 1111, 4097)]
+    lib = binding.load()
+    for (m, n, k), (_, _, _, nbytes) in zip(shapes, ask([f"plan {m} {n} {k}" for m, n, k in shapes])):
+        least = (((m + 15) // 16 * 16 * k * 2) + 255) // 256 * 256
+        assert lib.massv_linear_workspace(m, n, k, binding.BF16) == least + nbytes, (m, n, k)
