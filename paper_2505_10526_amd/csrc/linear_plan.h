@@ -45,10 +45,15 @@ inline int mixed_big(int M, int N) {
 // instead of 70), 60 x 18944 -> 3584 330 -> 36 us (K in twelve).
 // The square tile came later: its three coefficients are fitted alone, to the choice among all plans of 6756 shapes (17 widths, 30 to 3640
 // rows, weights from memory) whose taller plans stayed as they were.  It takes 71 % of them, 1.17 times as fast in the mean there (1 to 64
-// workgroups 1.27, 193 to 256 1.13; 1 % of all shapes are more than 2 % slower, at worst 1.2 times: long K from memory at 160 workgroups and
-// more).  1111 x 3584 -> 3584 43.6 -> 32.6 us, 128 x 1536 -> 8960 18.1 -> 13.5, 300 x 3584 -> 3584 23.7 -> 21.0.
-// The one of 192 rows in the same way, over 3861 shapes: 16 % take it, 1.07 times as fast in the mean there (0.6 % more than 2 % slower, at worst
-// 1.06 times).  1225 x 5120 -> 3584 62.9 -> 52.2 us, 1111 x 3584 -> 4608 48.9 -> 40.7.
+// workgroups 1.27, 193 to 256 1.13).  1111 x 3584 -> 3584 43.6 -> 32.6 us, 128 x 1536 -> 8960 18.1 -> 13.5, 300 x 3584 -> 3584 23.7 -> 21.0.
+// The one of 192 rows in the same way, over 3861 shapes: 16 % take it, 1.07 times as fast in the mean there.  1225 x 5120 -> 3584 62.9 -> 52.2 us,
+// 1111 x 3584 -> 4608 48.9 -> 40.7.
+// Over 5800 shapes drawn since (22 widths, 17 to 3640 rows, every copy of the weights read once a round), two cards, the calls that take either of the two:
+// median 1.12 and 1.10 times as fast as by 256-feature tiles, 3 and 9 % of them more than 2 % slower; nearly all of these have up to 64 rows and K in
+// several ranges, where the same shape is faster on one card and slower on the other (26 x 3840 -> 15360 30.3 and 35.5 us on one; median over
+// such calls 1.11 and 1.06), or an estimate within 2 % of the other plan's.
+// The one kind that lost on every card, many unsplit squares over a long K, is estimated 10 % higher: 500 calls of 8 widths that this takes from the squares
+// run 0.97 to 1.20 times as fast, 1.07 in the median (1144 x 18944 -> 3584 1.18, 385 to 512 x 5120 -> 5120 1.10, 769 to 1024 x 11008 -> 4096 1.03).
 inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
     const int big = mixed_big(M, N);
     if (big) return {4, 1, big};
@@ -70,6 +75,7 @@ inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
             const double all = (double)wgs / 256.0 * (stages * busy + ends), stream = (double)N * K * 2.0 / 8.5e6;
             if (all > t) t = all;
             if (stream > t) t = stream;
+            if (fj == 1 && parts == 1 && wgs > 128 && (K > 10000 || (K >= 5120 && wgs <= 160))) t *= 1.1;
             if (parts > 1) t += 3.0 + bytes / 2.6e6;
             if (t < best_t) { best_t = t; best.fj = fj; best.parts = parts; }
         }
