@@ -366,10 +366,13 @@ void prefill_attention_kernel(PrefillParams p) {
 // half as long and every SIMD has two.  All in vector registers (211 at d = 128; with the sums in accumulation registers, 128 and
 // 126, the moves between them ate the gain: 1000 rows on 6000 93 us).  28 / 4 heads of 128, one half and two: 1 x 1111 rows 30.3 and 26.9 us,
 // 1 x 800 24.2 and 21.2, 1000 on 6000 108.4 and 85.8, 16 on 8000 133.7 and 101.9; 14 / 2 heads of 64, 1 x 1111 22.1 and 17.2, 1000 on 6000
-// 79.7 and 52.9.  Under kPfCutBlocks blocks the first group does it alone (200 rows, 7 blocks: 10.0 us, cut 11.8).
+// 79.7 and 52.9.  Under pf_cut_blocks blocks the first group does it alone: setting up the second ring and putting the sums together takes 1 to 2 us (28 / 4
+// heads of 128, 292 rows on 35, 11 blocks: in one piece 14.4 us, cut 15.8).  Cut against one piece over 1300 calls that fit the chip, medians by blocks of keys: d = 128 10 to
+// 13 blocks 0.95 to 0.97 times as fast, 16 and 17 1.01, 18 1.03, 24 1.08; d = 64 10 to 13 blocks 0.98 to 1.01, 14 1.05, 24 1.13.  As it is, none of 1300 calls of 8 to 26
+// blocks is slower than by four waves alone (0.99 to 1.36).
 // ---------------------------------------------------------------------------
 constexpr int kPfRing = 4;
-constexpr int kPfCutBlocks = 10;
+constexpr int pf_cut_blocks(int D) { return D == 64 ? 10 : 18; }
 constexpr size_t pf_lds_bytes(int D) { return (size_t)kPfRing * 2 * kPfBlk * D * sizeof(bf16_t); }      // 64 KB at d = 128
 
 template <int D, bool DIRECT, int HALVES>
@@ -402,7 +405,7 @@ void prefill_attention_lds_kernel(PrefillParams p) {
     // blocks of the workgroup (visibility moves up with the row), of this half of it (few are not worth a second one), and of this wave
     const int all_begin = pf_lo(L + pos_of(w0), W) / kPfBlk;
     const int all_end = (pf_hi(L + pos_of(w0 + kPfWaves * 32 - 1), m_bidir, total) + kPfBlk - 1) / kPfBlk;
-    const int cut = HALVES == 1 || all_end - all_begin < kPfCutBlocks ? all_end : (all_begin + all_end + 1) / 2;
+    const int cut = HALVES == 1 || all_end - all_begin < pf_cut_blocks(D) ? all_end : (all_begin + all_end + 1) / 2;
     const int blk_begin = half ? cut : all_begin, blk_end = half ? all_end : cut;
     int blk_first = min_lo / kPfBlk, blk_last = (max_hi - 1) / kPfBlk;
     const bool whole = HALVES == 1 || cut == all_end;

@@ -138,9 +138,11 @@ def test_rows_and_blocks_through_lds(heads, kv_len, n_new, window, bidir, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("kv_len,n_new,window,bidir", [
-    ([270, 300, 310], [18, 20, 40], 0, False),          # 9, 10 and 11 blocks of keys: in one piece, in equal halves and in halves that differ by one
+    ([270, 300, 310], [18, 20, 40], 0, False),          # 9, 10 and 11 blocks of keys: d = 64 in one piece, in equal halves and in halves that differ by one
+    ([520, 556, 570], [24, 20, 38], 0, False),          # 17, 18 and 19: d = 128
     ([640, 400, 0], [70, 3, 33], 0, False),             # two workgroups of a pair, waves without rows, one without keys to cut
     ([700, 420, 352], [64, 65, 1], 330, False),         # windows that open inside the first half
+    ([900, 720, 652], [64, 65, 1], 600, False),         # the same with 18 blocks and more left
     ([0, 40, 0], [400, 350, 321], 0, True)])            # an image block that sees itself across the cut
 def test_keys_in_two_halves(kv_len, n_new, window, bidir, d):
     """Launches that fit the chip: the later half of a workgroup's key blocks belongs to a second group of waves."""
