@@ -1040,13 +1040,15 @@ extern "C" int massv_prefill_attention(const massv_attn_desc* desc, const void* 
     // 6000: 0.95).  At d = 128 it does so, in halves, for fresh prompts of up to 512 workgroups, whose many short key ranges fill up
     // what the long ones leave (64 rows a wave and halves: 28 / 4 heads, 4 x 300 20.0 and 14.8 us, 1 x 1500 39.6 and 34.1, 2 x 1000 32.3 and
     // 30.9, 544 workgroups 22.6 and 24.2; 16 / 8 heads, 2 x 2000 61.4 and 47.9, 752 workgroups 89.0 and 95.5; with a cache as long as the
-    // prompt or longer 47.2 and 48.9, 62.8 and 70.3).
+    // prompt or longer 47.2 and 48.9, 62.8 and 70.3).  Over 700 such calls (1 to 8 heads a KV head, 100 to 4000 rows) it is 1.16 times as fast in the median, but
+    // with 3 or 4 tiles a pair there are no long ranges to fill up behind: where their workgroups of 256 rows just fit the chip, those took 0.88 to 1.03 of
+    // the time (16 heads, 8 x 341 on 82 cached 21.7 and 24.7 us), with 192 of them 1.01 to 1.20.
     const int64_t pairs = (int64_t)a.batch * a.n_kv_heads, rows = (int64_t)a.n_query * (a.n_q_heads / a.n_kv_heads);
     const int64_t wide = pairs * ((rows + kPfWaves * 64 - 1) / (kPfWaves * 64)), tiles = (rows + kPfWaves * 32 - 1) / (kPfWaves * 32);
     const bool banded = a.window > 0 && a.window < a.l_max;
     bool halves = pairs * tiles <= 256;
     if (a.head_dim == 128)
-        halves = halves || (!banded && !n_bidir && pairs * tiles <= 512 && (a.n_query >= 256 || tiles >= 24) &&
+        halves = halves || (!banded && !n_bidir && pairs * tiles <= 512 && (tiles > 4 || wide <= 224) && (a.n_query >= 256 || tiles >= 24) &&
                              (int64_t)a.l_max * 4 <= (int64_t)a.n_query * 5 + 128);
     const bool few = halves || (a.head_dim == 64 && !banded && wide <= 256 && a.l_max / 8 <= a.n_query);
     switch (a.head_dim) {

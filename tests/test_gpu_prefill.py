@@ -183,11 +183,23 @@ def test_block_ring_d256(blocks, n_new, window):
 @pytest.mark.parametrize("d,heads,n_new", [
     (64, (1, 1), [512] * 129), (64, (7, 1), [292] * 32), (64, (7, 1), [292] * 33),      # 258, 256 and 264 workgroups of 256 rows
     (128, (1, 1), [128] * 256), (128, (1, 1), [128] * 257), (128, (1, 1), [129] * 200),      # 256, 257 and 400 of 128
-    (128, (8, 1), [384] * 11), (128, (8, 1), [368] * 12)])                              # 24 and 23 tiles of 128 rows a pair
+    (128, (8, 1), [384] * 11), (128, (8, 1), [368] * 12)])                              # 264 and 276 of more than 256 positions
 def test_both_sides_of_the_launch_size_rule(d, heads, n_new):
     """Launches just inside and just outside the rules that choose between 32 and 64 rows per wave."""
     s = synth.LayerShape(256, heads[0], heads[1], d, 704, 4096, dtype="bf16")
     run_case(s, [0] * len(n_new), n_new, [9] * len(n_new), seed=len(n_new), check=[0, len(n_new) - 1])
+
+
+@pytest.mark.parametrize("heads,kv_len,n_new,pairs", [
+    ((1, 1), 0, 640, 102), ((1, 1), 0, 640, 103),              # 510 and 515 workgroups of 128 rows
+    ((1, 1), 0, 384, 85), ((1, 1), 0, 384, 128), ((1, 1), 0, 512, 112), ((1, 1), 0, 512, 113),        # 3 and 4 tiles a pair: 170 and 256, 224 and 226 of 256 rows
+    ((3, 1), 0, 256, 50), ((3, 1), 0, 255, 50),                # 256 and 255 positions, 6 tiles a pair
+    ((16, 1), 0, 185, 11), ((16, 1), 0, 184, 12),              # 24 and 23 tiles a pair, fewer positions
+    ((2, 1), 96, 256, 75), ((2, 1), 97, 256, 75)])             # a cache a quarter longer than the prompt and 32 rows, and a block more
+def test_both_sides_of_the_fresh_prompt_rule(heads, kv_len, n_new, pairs):
+    """d = 128, launches of more than 256 workgroups: each limit of the rule that gives fresh prompts to the kernel of 32 rows a wave."""
+    s = synth.LayerShape(256, heads[0], heads[1], 128, 704, 4096, dtype="bf16")
+    run_case(s, [kv_len] * pairs, [n_new] * pairs, [9] * pairs, seed=pairs, check=[0, pairs - 1])
 
 
 @pytest.mark.parametrize("d", [64, 128, 256])
