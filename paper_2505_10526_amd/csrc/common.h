@@ -61,12 +61,12 @@ __device__ inline float4 ldg_stream(const float4* p) {
 // ---- stores past the L2 ----
 // What a kernel leaves dirty in the dies' L2s (4 MB each) is written back when it ends, with nothing else going on, and while it runs a
 // stream of weights pushes it out in halves of lines.  Written through (agent scope), results go out as they come.  It pays where a launch that
-// reads far more than the caches hold leaves megabytes of results: see where it is used.  The wait state is for the registers of a
-// 16-byte store, which the compiler does not see to be one.
+// reads far more than the caches hold leaves megabytes of results: see where it is used.  gfx950 takes the data of a 16-byte store out of its registers
+// up to two wait states after the issue; the compiler, which puts these in by itself, does not see the assembly to be a store.
 template <typename V>
 __device__ inline void store_through(V* p, V v) {
     static_assert(sizeof(V) == 16, "");
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
 }
 
 // ---- operand-order ("packed") activations ----
