@@ -138,10 +138,12 @@ void gemm_vocab_kernel(GemmDev g) {
     for (int mt = 0; mt < MT; ++mt) { best_v[mt] = -INFINITY; best_i[mt] = INT_MAX; sum_e[mt] = 0.0; }
 
     // Logits of more than 16 rows are written through L2 (store_through); fewer rows stay there for the accept rule, which reads them next (6 rows of
-    // 152064 191 us either way, one row 88.4 and 89.3 us a call).
+    // 152064 191 us either way, one row 88.4 and 89.3 us a call).  The line is drawn by rows, not by bytes, as few logits lose nothing: 4096 to 32000 of 17 to 64
+    // rows (512 to 5120 wide, 500 calls) are 0.96 to 1.07 times as fast written through as cached, medians 1.00 to 1.02, 65536 1.01 to 1.03, 152064 1.03.  Plain
+    // logits of 17 to 32 rows, one share a workgroup, stay in L2: written through, 12000 to 40000 of them were 0.976 to 0.99 times as fast in the medians (4096 1.007).
     auto put_logits = [&](int m, int col, floatx4 v) {
         floatx4* dst = reinterpret_cast<floatx4*>((float*)g.y + (size_t)m * g.ldy + col);
-        if constexpr (MT > 1) store_through(dst, v);
+        if constexpr (MT > 2 || (MT > 1 && (MANY || STATS))) store_through(dst, v);
         else *dst = v;
     };
     // Barrier for what travels through LDS; loads on their way into registers stay on their way.
@@ -506,7 +508,8 @@ int gemm_supported(const GemmArgs& g) {
 //   X, re-read from L2 once per workgroup column: (T / nt) * K/32 * MT KB, at 14 TB/s;
 //   0.8 us per MB of partial sums (written here, read back by the next kernel).  Of more than 16 rows they are written through L2
 //   (store_through): 48-row layer 126.0 -> 125.3 us (128.2 -> 126.0 on another card), 28 rows of a drafter 1538 -> 1528; of 6 and 10 rows 100.1 and 110.5 us cached,
-//   100.2 and 110.9 through.
+//   100.2 and 110.9 through.  Whole layers of 17 to 64 rows, 256 to 5120 wide, 300 calls: 0.98 to 1.02 times as fast as with cached sums, medians by width and rows 0.99
+//   (256 wide, 64 rows) to 1.015; narrow ones, whose few hundred KB are read back at once, lose nothing either.
 // Measured against the earlier rule "as many slabs as fill 256 workgroups, largest tile count": q/k/v (8 tiles, 7
 // slabs) -> (4, 3) -1.9 us, output projection (7, 7) -> (4, 4) -1.0 us, down projection (7, 8) unchanged.
 static GemmPlan plan_split(const GemmArgs& g, int mt, int T) {

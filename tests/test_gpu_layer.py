@@ -528,6 +528,24 @@ def test_vocabulary_maximum_that_never_and_always_moves(M, rising):
     assert torch.equal(l1.view(M, V), logits) and torch.equal(n1, n2) and torch.equal(t1, t2)
 
 
+@pytest.mark.parametrize("M", [16, 17, 32, 33])
+@pytest.mark.parametrize("V", [4096, 32000, 50000, 81328])
+def test_logits_past_the_cache_and_through_it(M, V):
+    """Two row tiles with one share a workgroup stay in L2 as plain logits and go past it beside the accept rule, and with more shares (or one row tile
+    more) both go past it: the same bits, and against float64 within fp32 sums of H products (sqrt(H) roundings of 2^-24, four times)."""
+    H = 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + V)
+    x, w = (torch.randn(n, H, generator=g, device="cuda").to(torch.bfloat16) for n in (M, V))
+    room = torch.full((M * V + 4096,), 7.0, device="cuda")
+    wp = binding.weight_pack(w)
+    logits = binding.lm_head_logits(x, None, wp, out=room[:M * V].view(M, V))
+    assert (room[M * V:] == 7).all()
+    ref = x.double() @ w.double().T
+    assert (logits.double() - ref).abs().max() / ref.abs().max() <= 4 * H ** 0.5 * 2.0 ** -24
+    assert torch.equal(binding.lm_head_accept(x.view(M, 1, H), None, wp, None, None, torch.full((M, 1), 0.5, device="cuda"), 1.0)[2].view(M, V), logits)
+
+
 @pytest.mark.parametrize("H", [7, 64, 68, 252, 256, 260, 512, 700, 1028])
 @pytest.mark.parametrize("M,V", [(1, 100), (2, 4097), (3, 33), (4, 5000), (5, 70), (8, 4096), (9, 4100), (17, 64)])
 def test_fp32_logits_rows_and_widths(M, V, H):
