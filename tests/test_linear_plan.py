@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_linear as shapes
 from paper_2505_10526_amd import binding
 
 CSRC = os.path.join(os.path.dirname(binding.__file__), "csrc")
@@ -83,3 +84,18 @@ def test_the_library_asks_for_that_room(ask):
                                             (600, 5120, 5120, 1, 1), (700, 3584, 5120, 1, 1), (600, 3584, 4608, 1, 1), (1000, 3584, 3584, 1, 1), (530, 3840, 3840, 1, 1)])
 def test_tile_of_long_k(ask, M, N, K, fj, parts):
     assert ask([f"plan {M} {N} {K}"])[0][:3] == (fj, parts, 0)
+
+
+@pytest.mark.parametrize("name,fj,split", [("TALL", 4, False), ("TALL_SPLIT", 4, True), ("SQUARE", 1, False), ("SQUARE_SPLIT", 1, True), ("LOW192", 3, False),
+                                           ("LOW192_SPLIT", 3, True), ("FLAT", 2, False), ("FLAT_SPLIT", 2, True)])
+def test_shapes_of_the_tile_tests_take_their_tiles(ask, name, fj, split):
+    """The lists of test_gpu_linear.py are there for one tile each; split ones with ranges of K of unequal length among them."""
+    listed = getattr(shapes, name)
+    got = ask([f"plan {m} {n} {k}" for m, n, k in listed])
+    assert all((f, p > 1, big) == (fj, split, 0) for f, p, big, _ in got), list(zip(listed, got))
+    assert not split or sum(k // 64 % p != 0 for (_, _, k), (_, p, _, _) in zip(listed, got)) >= 2
+
+
+def test_shapes_of_both_heights_end_in_halves(ask):
+    got = ask([f"plan {m} {n} {k}" for m, n, k in shapes.MIXED])
+    assert [s for s, (_, _, big, _) in zip(shapes.MIXED, got) if not big] == [(6145, 4096, 64)]       # (a row of tiles too many)
