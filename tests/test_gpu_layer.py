@@ -510,18 +510,26 @@ def test_vocabulary_statistics_carried_across_shares_keep_small_terms():
 @pytest.mark.parametrize("rising", [False, True], ids=["equal", "rising"])
 @pytest.mark.parametrize("M", [5, 16, 17, 48, 64])
 def test_vocabulary_maximum_that_never_and_always_moves(M, rising):
-    """Statistics of rows whose logits are all equal (the first column holds the maximum from the start) and of rows that rise with the
-    column (every piece of every share brings a new maximum), at one to four row tiles and three shares a workgroup: the greedy
+    """Statistics of rows whose logits are all equal (the first column holds the maximum from the start) and of rows that rise from each tile of 16
+    columns to the next (every piece of every share brings a new maximum), at one to four row tiles and three shares a workgroup: the greedy
     token, and at T = 1 the same integers as from the logits themselves."""
     H, V = 64, 81328
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     x = torch.rand(M, H, generator=g, device="cuda").to(torch.bfloat16) + 0.25            # positive: a row's logits follow the weights
-    w = (torch.arange(V, device="cuda") * (16.0 / V) if rising else torch.ones(V, device="cuda"))[:, None].expand(V, H).to(torch.bfloat16).contiguous()
+    w = torch.zeros(V, H, device="cuda")
+    if rising:                # tile t = 72 c + f: c and f are exact in bf16, and 72 steps of the fine column are less than one of the coarse ones
+        t = torch.arange(V, device="cuda") // 16
+        w[:, 0], w[:, 1:] = (t % 72) / 512, (t // 72)[:, None] / 64
+    else:
+        w[:] = 1
+    w = w.to(torch.bfloat16).contiguous()
     wp = binding.weight_pack(w)
     n, tok = binding.lm_head_greedy_accept(x.view(M, 1, H), None, wp, None)
     logits = binding.lm_head_logits(x, None, wp)
     assert torch.equal(tok.view(-1).long(), logits.argmax(-1)) and (rising or not tok.any())
+    top = logits.view(M, V // 16, 16).amax(-1)
+    assert (top[:, 1:] > top[:, :-1]).all() == rising
     u = torch.rand(M, 1, generator=g, device="cuda") * 0.999
     n1, t1, l1 = binding.lm_head_accept(x.view(M, 1, H), None, wp, None, None, u, 1.0)
     n2, t2 = binding.spec_accept(logits.view(M, 1, V), None, None, u, 1.0)
