@@ -222,3 +222,28 @@ def test_caches_that_start_anywhere(heads, n_new, d):
         out.append(binding.prefill_attention(put(q), put(k), put(v), i32(kv_len), i32(n_new), out=put(torch.zeros_like(q))))
     torch.cuda.synchronize()
     assert out[0].abs().sum() > 0 and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("n_new,windowed,bidir", [(64, False, False), (66, False, False), (30, False, False), (64, True, False), (0, False, True)])
+def test_halves_from_caches_that_start_anywhere(n_new, windowed, bidir, more, d):
+    """The fewest blocks of keys that are cut into halves, and one more (halves that differ by one), from caches one and four elements off a multiple of 16 bytes:
+    both rings are then filled through registers, with the same bits.  All waves busy, one wave of a second workgroup, idle waves, a window that
+    leaves blocks out at the front, and a whole prompt with an image block that sees itself across the cut."""
+    blocks = (10 if d == 64 else 18) + more
+    total = 32 * blocks - 5 + (96 if windowed else 0)
+    n_new = n_new or total
+    window, n_bidir = (32 * blocks - 40 if windowed else 0), (i32([total - 40]) if bidir else None)
+    s = synth.LayerShape(256, 4, 2, d, 704, 4096, dtype="bf16")
+    run_case(s, [total - n_new], [n_new], [total - 40 if bidir else 9], seed=blocks + n_new, window=window, bidir=bidir)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(total)
+    rn = lambda *shape: torch.randn(*shape, generator=g, device="cuda").to(torch.bfloat16)
+    l_max = round_up(total, 32)
+    q, k, v = rn(1, n_new, 4, d), rn(1, 2, l_max, d), rn(1, 2, l_max // 32, d, 32)
+    out = []
+    for off in (0, 1, 4):
+        kv = [torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)[off:off + t.numel()].view(t.shape).copy_(t) for t in (k, v)]
+        out.append(binding.prefill_attention(q, kv[0], kv[1], i32([total - n_new]), i32([n_new]), n_bidir, window=window))
+    assert out[0].abs().sum() > 0 and torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
