@@ -9,8 +9,8 @@
 // relative size as rounding the normalised row.
 //
 // Bound by latency where the weights are few (an empty launch, one trip to memory, the sum over the waves), by L2 and HBM
-// where they are many: a workgroup reads all of X for its 8, 16 or 32 features, and L2 feeds the compute units at about
-// 14 TB/s together and 60 GB/s each.  Hence 16 waves that take the 32-wide steps of K in turn with all loads of U steps in flight
+// where they are many: a workgroup reads all of X for its 8, 16 or 32 features, which here comes at about
+// 14 TB/s together and 60 GB/s a compute unit (L2 hits alone, with nothing else under way: 32 TB/s and 150 GB/s).  Hence 16 waves that take the 32-wide steps of K in turn with all loads of U steps in flight
 // (a workgroup of 4 waves with fewer loads each took one more trip to memory), one round of workgroups, and the rules below on how many
 // rows and features are worth it.  The operand rows past M are not fetched.
 // us a layer in a stack, slabs and this, in turn on one card: 1.5B shape, 8 rows 48.3 -> 39.5, 16 rows 49.3 -> 45.8; 7B shape, 6 rows
