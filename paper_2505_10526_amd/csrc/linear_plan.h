@@ -8,10 +8,16 @@ namespace massv {
 
 constexpr int kLinTile = 256;            // features and rows of the largest tile
 
-// Tiles of 256 features x 64 fj rows (fj = 4 or 2) or of 128 x 128 (1) or 192 (3), and ranges of K, for one call whose partial sums may take `room`
-// bytes.
-// big: 0, or that many tiles of 256 rows followed by halves (linear_mixed_kernel).
-struct LinPlan { int fj, parts, big; };
+// The tiles of massv_linear, by the number that stands for each in a plan and in a kernel's name, and the coefficients of linear_best's estimate: microseconds
+// a 32-wide stage of one, its share of the chip's power, and its two ends.
+struct LinShape { int features, rows; double stage, busy, ends; };
+constexpr LinShape kLinShapes[5] = {{}, {128, 128, 0.18, 0.203, 1.92}, {256, 128, 0.27, 0.353, 1.75}, {128, 192, 0.261, 0.235, 1.66}, {256, 256, 0.54, 0.625, 1.4}};
+constexpr int kLinSquare = 1, kLinFlat = 2, kLinLow = 3, kLinTall = 4;
+constexpr int lin_tiles_m(int tile, int M) { return (M + kLinShapes[tile].rows - 1) / kLinShapes[tile].rows; }
+constexpr int lin_tiles_n(int tile, int N) { return (N + kLinShapes[tile].features - 1) / kLinShapes[tile].features; }
+
+// One call: its tile and the number of ranges of K.  big: 0, or that many of the tallest tiles followed by halves (linear_mixed_kernel).
+struct LinPlan { int tile, parts, big; };
 
 inline int mixed_tiles_m(int M) { return M / kLinTile + (M % kLinTile > kLinTile / 2); }
 inline int mixed_halves(int M, int N, int big) {         // (of at most 128 tiles that are left)
@@ -22,6 +28,7 @@ inline int mixed_halves(int M, int N, int big) {         // (of at most 128 tile
 // long.  1.025 to 1.14 times as fast as the better of the two heights on all of 36 drawn shapes that take it (1 to 10 rounds, 1536 to
 // 18944 wide, weights from memory; 1111 x 3584 -> 18944 158 -> 145 us, 16384 x 18944 -> 3584 1755 -> 1673, 6021 x 18944 -> 3584
 // 768 -> 673, 10251 x 3840 -> 15360 981 -> 955); with 1.01 to 1.17 rounds of halves left 0.95 to 1.007 times.
+// (The estimate, which has the 128-feature tiles besides, is not asked here: against it, over 147 drawn shapes, 0.89 to 1.14 times as fast, 1.06 in the median.)
 inline int mixed_big(int M, int N) {
     const int64_t tiles = (int64_t)mixed_tiles_m(M) * ((N + 255) / 256);
     const int big = (int)(tiles / 256 * 256);
@@ -56,28 +63,26 @@ inline int mixed_big(int M, int N) {
 // run 0.97 to 1.20 times as fast, 1.07 in the median (1144 x 18944 -> 3584 1.18, 385 to 512 x 5120 -> 5120 1.10, 769 to 1024 x 11008 -> 4096 1.03).
 inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
     const int big = mixed_big(M, N);
-    if (big) return {4, 1, big};
-    LinPlan best = {4, 1, 0};
+    if (big) return {kLinTall, 1, big};
+    LinPlan best = {kLinTall, 1, 0};
     double best_t = 1e300;
-    for (int fj = 4; fj >= 1; --fj) {
-        if (fj % 2 && !square) continue;
-        const int rows = fj >= 3 ? 64 * fj : 128, cols = fj % 2 ? 128 : 256;
-        const int64_t tiles = (int64_t)((M + rows - 1) / rows) * ((N + cols - 1) / cols);
-        if (fj != 4 && tiles > (1 << 20)) break;
-        const double stage = fj == 4 ? 0.54 : fj == 3 ? 0.261 : fj == 2 ? 0.27 : 0.18, busy = fj == 4 ? 0.625 : fj == 3 ? 0.235 : fj == 2 ? 0.353 : 0.203;
-        const double ends = fj == 4 ? 1.4 : fj == 3 ? 1.66 : fj == 2 ? 1.75 : 1.92;
+    for (int tile = kLinTall; tile >= kLinSquare; --tile) {
+        const LinShape& s = kLinShapes[tile];
+        if (s.features == 128 && !square) continue;
+        const int64_t tiles = (int64_t)lin_tiles_m(tile, M) * lin_tiles_n(tile, N);
+        if (tile != kLinTall && tiles > (1 << 20)) break;
         for (int parts = 1; parts <= 32 && parts <= K / 64; ++parts) {
             const double bytes = (double)parts * M * N * 4.0;
             if (parts > 1 && (tiles * parts > 560 || bytes > (double)room)) break;
             const int64_t wgs = tiles * parts;
             const double stages = 2.0 * ((K / 64 + parts - 1) / parts);
-            double t = (double)((wgs + 255) / 256) * (stages * stage + ends);
-            const double all = (double)wgs / 256.0 * (stages * busy + ends), stream = (double)N * K * 2.0 / 8.5e6;
+            double t = (double)((wgs + 255) / 256) * (stages * s.stage + s.ends);
+            const double all = (double)wgs / 256.0 * (stages * s.busy + s.ends), stream = (double)N * K * 2.0 / 8.5e6;
             if (all > t) t = all;
             if (stream > t) t = stream;
-            if (fj == 1 && parts == 1 && wgs > 128 && (K > 10000 || (K >= 5120 && wgs <= 160))) t *= 1.1;
+            if (tile == kLinSquare && parts == 1 && wgs > 128 && (K > 10000 || (K >= 5120 && wgs <= 160))) t *= 1.1;
             if (parts > 1) t += 3.0 + bytes / 2.6e6;
-            if (t < best_t) { best_t = t; best.fj = fj; best.parts = parts; }
+            if (t < best_t) { best_t = t; best = {tile, parts, 0}; }
         }
     }
     return best;

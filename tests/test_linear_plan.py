@@ -25,7 +25,7 @@ int main() {
     while (scanf("%15s", what) == 1) {
         if (!strcmp(what, "plan") && scanf("%d %d %d", &a, &b, &c) == 3) {
             const LinPlan p = linear_plan(a, b, c, linear_asked_room(a, b, c));
-            printf("%d %d %d %zu\n", p.fj, p.parts, p.big, linear_asked_room(a, b, c));
+            printf("%d %d %d %zu\n", p.tile, p.parts, p.big, linear_asked_room(a, b, c));
         } else if (!strcmp(what, "rooms") && scanf("%d %d %d %d", &a, &b, &c, &d) == 4) {
             int bad = 0, split = 0;
             for (int M = a; M <= b; ++M) {
