@@ -55,12 +55,16 @@ inline int mixed_big(int M, int N) {
 // workgroups 1.27, 193 to 256 1.13).  1111 x 3584 -> 3584 43.6 -> 32.6 us, 128 x 1536 -> 8960 18.1 -> 13.5, 300 x 3584 -> 3584 23.7 -> 21.0.
 // The one of 192 rows in the same way, over 3861 shapes: 16 % take it, 1.07 times as fast in the mean there.  1225 x 5120 -> 3584 62.9 -> 52.2 us,
 // 1111 x 3584 -> 4608 48.9 -> 40.7.
-// Over 5800 shapes drawn since (22 widths, 17 to 3640 rows, every copy of the weights read once a round), two cards, the calls that take either of the two:
-// median 1.12 and 1.10 times as fast as by 256-feature tiles, 3 and 9 % of them more than 2 % slower; nearly all of these have up to 64 rows and K in
-// several ranges, where the same shape is faster on one card and slower on the other (26 x 3840 -> 15360 30.3 and 35.5 us on one; median over
-// such calls 1.11 and 1.06), or an estimate within 2 % of the other plan's.
-// The one kind that lost on every card, many unsplit squares over a long K, is estimated 10 % higher: 500 calls of 8 widths that this takes from the squares
-// run 0.97 to 1.20 times as fast, 1.07 in the median (1144 x 18944 -> 3584 1.18, 385 to 512 x 5120 -> 5120 1.10, 769 to 1024 x 11008 -> 4096 1.03).
+// Over 2500 shapes drawn since (31 widths, 17 to 3700 rows, weights from memory) whose plan is another than among the 256-feature tiles: 1.12 times as fast as by those in the median
+// (0.87 to 1.46), 0.9 % of them more than 2 % slower; nearly all of these have up to 64 rows and K in several ranges, where the same shape is faster on one card
+// and slower on another (30 x 3840 -> 15360 0.87, the median over such calls 1.03).
+// Kinds that lost to the plans of before on the cards they were timed on are estimated higher, and so go back to those (weights from memory, each call 16 times in turn).
+//   Many unsplit squares over a long K, by 10 %: 500 calls of 8 widths that this takes from the squares run 0.97 to 1.20 times as fast, 1.07 in the median
+//   (1144 x 18944 -> 3584 1.18, 385 to 512 x 5120 -> 5120 1.10, 769 to 1024 x 11008 -> 4096 1.03).
+//   Unsplit squares whose last row tile is more than half full, over a long K or fewer than the chip has units, by 25 %.  Rows past the last one cost a tile
+//   next to nothing, and the squares' time grows faster with the rows that are there: 4096 -> 6144, three row tiles, by squares and by 256 x 128 with K in three 31.5 and
+//   32.4 us with 262 rows, 33.8 and 34.0 with 300, 40.0 and 36.6 with 378; 8192 -> 3072, nine row tiles, K in two 64.7 and 67.0 us with 1065 rows, 76.0 and 70.5 with 1145.
+//   Over 700 such calls of 20 widths on three cards 0.97 to 1.25 times as fast as by the squares, 1.05 in the median.
 inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
     const int big = mixed_big(M, N);
     if (big) return {kLinTall, 1, big};
@@ -80,7 +84,9 @@ inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
             const double all = (double)wgs / 256.0 * (stages * s.busy + s.ends), stream = (double)N * K * 2.0 / 8.5e6;
             if (all > t) t = all;
             if (stream > t) t = stream;
+            const bool full = (M - 1) % s.rows >= s.rows / 2;
             if (tile == kLinSquare && parts == 1 && wgs > 128 && (K > 10000 || (K >= 5120 && wgs <= 160))) t *= 1.1;
+            if (tile == kLinSquare && parts == 1 && full && (K > 8000 || (wgs <= (K >= 5120 ? 160 : 152) && M > 128 && K >= 2048 && K >= 24 * wgs))) t *= 1.25;
             if (parts > 1) t += 3.0 + bytes / 2.6e6;
             if (t < best_t) { best_t = t; best = {tile, parts, 0}; }
         }

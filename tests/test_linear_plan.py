@@ -81,8 +81,16 @@ def test_the_library_asks_for_that_room(ask):
 
 # unsplit squares over a long K were 2 to 18 % slower in these than 256 x 128 (or 192 x 128) with K in two (or three); and neighbours where they are the faster ones
 @pytest.mark.parametrize("M,N,K,fj,parts", [(1000, 3840, 15360, 2, 2), (1148, 3584, 18944, 2, 2), (460, 5120, 5120, 3, 2), (900, 4096, 11008, 2, 2), (1800, 2048, 16384, 2, 2),
-                                            (600, 5120, 5120, 1, 1), (700, 3584, 5120, 1, 1), (600, 3584, 4608, 1, 1), (1000, 3584, 3584, 1, 1), (530, 3840, 3840, 1, 1)])
+                                            (600, 5120, 5120, 1, 1), (700, 3584, 5120, 1, 1), (1000, 3584, 3584, 1, 1), (530, 3840, 3840, 1, 1)])
 def test_tile_of_long_k(ask, M, N, K, fj, parts):
+    assert ask([f"plan {M} {N} {K}"])[0][:3] == (fj, parts, 0)
+
+
+# the same by how full the last row tile is: squares took 40.0 us for 378 x 4096 -> 6144 and 256 x 128 with K in three 36.6, 31.5 and 32.4 for 262 rows; 76.0 and 70.5
+# for 1145 x 8192 -> 3072, 64.7 and 67.0 for 1065; 42.8 and 37.2 for 600 x 4608 -> 3584
+@pytest.mark.parametrize("M,N,K,fj,parts", [(378, 6144, 4096, 2, 3), (262, 6144, 4096, 1, 1), (1145, 3072, 8192, 2, 2), (1065, 3072, 8192, 1, 1), (600, 3584, 4608, 2, 3),
+                                            (630, 3584, 3584, 2, 3), (128, 18944, 3584, 1, 1)])
+def test_tile_of_full_rows(ask, M, N, K, fj, parts):
     assert ask([f"plan {M} {N} {K}"])[0][:3] == (fj, parts, 0)
 
 
