@@ -65,6 +65,8 @@ inline int mixed_big(int M, int N) {
 //   next to nothing, and the squares' time grows faster with the rows that are there: 4096 -> 6144, three row tiles, by squares and by 256 x 128 with K in three 31.5 and
 //   32.4 us with 262 rows, 33.8 and 34.0 with 300, 40.0 and 36.6 with 378; 8192 -> 3072, nine row tiles, K in two 64.7 and 67.0 us with 1065 rows, 76.0 and 70.5 with 1145.
 //   Over 700 such calls of 20 widths on three cards 0.97 to 1.25 times as fast as by the squares, 1.05 in the median.
+//   192-row tiles in two rounds whose last row tile is so, or over a long K, by 3 % (by the estimate a tie with one round of the tallest): 1900 such calls on four cards run 0.92 to 1.20
+//   times as fast by the tallest, 1.05, 0.99, 0.99 and 1.00 in the medians of the cards (2046 x 5120 -> 5120 113 us and by the tallest 105 on the first).
 inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
     const int big = mixed_big(M, N);
     if (big) return {kLinTall, 1, big};
@@ -87,6 +89,7 @@ inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
             const bool full = (M - 1) % s.rows >= s.rows / 2;
             if (tile == kLinSquare && parts == 1 && wgs > 128 && (K > 10000 || (K >= 5120 && wgs <= 160))) t *= 1.1;
             if (tile == kLinSquare && parts == 1 && full && (K > 8000 || (wgs <= (K >= 5120 ? 160 : 152) && M > 128 && K >= 2048 && K >= 24 * wgs))) t *= 1.25;
+            if (tile == kLinLow && parts == 1 && wgs <= 512 && (K > 8000 || (full && wgs > 256))) t *= 1.03;
             if (parts > 1) t += 3.0 + bytes / 2.6e6;
             if (t < best_t) { best_t = t; best = {tile, parts, 0}; }
         }

@@ -87,9 +87,9 @@ def test_tile_of_long_k(ask, M, N, K, fj, parts):
 
 
 # the same by how full the last row tile is: squares took 40.0 us for 378 x 4096 -> 6144 and 256 x 128 with K in three 36.6, 31.5 and 32.4 for 262 rows; 76.0 and 70.5
-# for 1145 x 8192 -> 3072, 64.7 and 67.0 for 1065; 42.8 and 37.2 for 600 x 4608 -> 3584
+# for 1145 x 8192 -> 3072, 64.7 and 67.0 for 1065; 42.8 and 37.2 for 600 x 4608 -> 3584; two rounds of 192 rows 113 for 2046 x 5120 -> 5120, one of 256 rows 105
 @pytest.mark.parametrize("M,N,K,fj,parts", [(378, 6144, 4096, 2, 3), (262, 6144, 4096, 1, 1), (1145, 3072, 8192, 2, 2), (1065, 3072, 8192, 1, 1), (600, 3584, 4608, 2, 3),
-                                            (630, 3584, 3584, 2, 3), (128, 18944, 3584, 1, 1)])
+                                            (630, 3584, 3584, 2, 3), (128, 18944, 3584, 1, 1), (2046, 5120, 5120, 4, 1), (1136, 4096, 11008, 4, 3)])
 def test_tile_of_full_rows(ask, M, N, K, fj, parts):
     assert ask([f"plan {M} {N} {K}"])[0][:3] == (fj, parts, 0)
 
