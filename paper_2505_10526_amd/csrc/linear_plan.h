@@ -67,6 +67,8 @@ inline int mixed_big(int M, int N) {
 //   Over 700 such calls of 20 widths on three cards 0.97 to 1.25 times as fast as by the squares, 1.05 in the median.
 //   192-row tiles in two rounds whose last row tile is so, or over a long K, by 3 % (by the estimate a tie with one round of the tallest): 1900 such calls on four cards run 0.92 to 1.20
 //   times as fast by the tallest, 1.05, 0.99, 0.99 and 1.00 in the medians of the cards (2046 x 5120 -> 5120 113 us and by the tallest 105 on the first).
+//   192-row tiles with K in two, by 2 %: 270 calls that this gives to 256 x 128 with K in three run 0.97 to 1.10 times as fast, 1.04 in the median; those that are ahead of K in two by
+//   256 x 128 (1.02 to 1.16) stay.
 inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
     const int big = mixed_big(M, N);
     if (big) return {kLinTall, 1, big};
@@ -91,6 +93,7 @@ inline LinPlan linear_best(int M, int N, int K, size_t room, bool square) {
             if (tile == kLinSquare && parts == 1 && full && (K > 8000 || (wgs <= (K >= 5120 ? 160 : 152) && M > 128 && K >= 2048 && K >= 24 * wgs))) t *= 1.25;
             if (tile == kLinLow && parts == 1 && wgs <= 512 && (K > 8000 || (full && wgs > 256))) t *= 1.03;
             if (parts > 1) t += 3.0 + bytes / 2.6e6;
+            if (tile == kLinLow && parts == 2) t *= 1.02;
             if (t < best_t) { best_t = t; best = {tile, parts, 0}; }
         }
     }
