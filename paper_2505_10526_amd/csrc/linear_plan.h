@@ -28,6 +28,7 @@ inline int mixed_halves(int M, int N, int big) {         // (of at most 128 tile
 // long.  1.025 to 1.14 times as fast as the better of the two heights on all of 36 drawn shapes that take it (1 to 10 rounds, 1536 to
 // 18944 wide, weights from memory; 1111 x 3584 -> 18944 158 -> 145 us, 16384 x 18944 -> 3584 1755 -> 1673, 6021 x 18944 -> 3584
 // 768 -> 673, 10251 x 3840 -> 15360 981 -> 955); with 1.01 to 1.17 rounds of halves left 0.95 to 1.007 times.
+// Over 260 shapes drawn since (31 widths, up to 16384 rows) 1.08 times as fast in the median (0.97 to 1.19; 1945 and 2027 x 1536 -> 8960 are the two below 1.0).
 // (The estimate, which has the 128-feature tiles besides, is not asked here: against it, over 147 drawn shapes, 0.89 to 1.14 times as fast, 1.06 in the median.)
 inline int mixed_big(int M, int N) {
     const int64_t tiles = (int64_t)mixed_tiles_m(M) * ((N + 255) / 256);
@@ -56,7 +57,7 @@ inline int mixed_big(int M, int N) {
 // The one of 192 rows in the same way, over 3861 shapes: 16 % take it, 1.07 times as fast in the mean there.  1225 x 5120 -> 3584 62.9 -> 52.2 us,
 // 1111 x 3584 -> 4608 48.9 -> 40.7.
 // Over 2500 shapes drawn since (31 widths, 17 to 3700 rows, weights from memory) whose plan is another than among the 256-feature tiles: 1.12 times as fast as by those in the median
-// (0.87 to 1.46), 0.9 % of them more than 2 % slower; nearly all of these have up to 64 rows and K in several ranges, where the same shape is faster on one card
+// (0.86 to 1.46), 0.9 and 1.7 % of them on two cards more than 2 % slower; nearly all of these have up to 64 rows and K in several ranges, where the same shape is faster on one card
 // and slower on another (30 x 3840 -> 15360 0.87, the median over such calls 1.03).
 // Kinds that lost to the plans of before on the cards they were timed on are estimated higher, and so go back to those (weights from memory, each call 16 times in turn).
 //   Many unsplit squares over a long K, by 10 %: 500 calls of 8 widths that this takes from the squares run 0.97 to 1.20 times as fast, 1.07 in the median
